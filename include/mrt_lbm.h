@@ -352,11 +352,12 @@ lbm_status lbm_set_timing(lbm_ctx *ctx, int32_t enable);
  * only, so a captured step stays capturable. */
 lbm_status lbm_set_write_check(lbm_ctx *ctx, int32_t enable);
 
-/* Cache policy of the split step's population stores (LBM_STEP_SPLIT; other
- * step modes always store cached).  LBM_STORE_AUTO (the default) stores
- * non-temporally when the two population arrays together exceed the GPU's
- * 256 MiB last-level cache, where cached stores would evict the lines the next
- * plane's reads need; LBM_STORE_CACHED and LBM_STORE_STREAM force either
+/* Cache policy of the population stores of the split step (LBM_STEP_SPLIT) and
+ * of the step of runs with walls on x or y (other step modes always store
+ * cached).  LBM_STORE_AUTO (the default) stores non-temporally when the two
+ * population arrays together exceed the GPU's 256 MiB last-level cache, where
+ * cached stores would evict the lines the next plane's reads need (with walls
+ * on x or y only if the direction planes start on 64 bytes); LBM_STORE_CACHED and LBM_STORE_STREAM force either
  * policy.  Results are bit for bit the same under every policy; only the
  * speed differs.  An unknown policy returns LBM_ERR_INVALID_ARG. */
 enum { LBM_STORE_AUTO = 0, LBM_STORE_CACHED = 1, LBM_STORE_STREAM = 2 };

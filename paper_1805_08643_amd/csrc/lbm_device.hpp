@@ -175,6 +175,8 @@ __device__ inline rsrc_t make_rsrc(const void *base, uint32_t bytes) {
 template <> struct Storage<ST_F64> {
     using T = double;
     using R = double;
+    __device__ static inline R dec(T v, R, R) { return v; }
+    __device__ static inline T enc(R v, R, R) { return v; }
     __device__ static inline R load(const T *p, R, R) { return __builtin_nontemporal_load(p); }
     __device__ static inline void store(T *p, R v, R, R) { __builtin_nontemporal_store(v, p); }
     __device__ static inline R ldb(rsrc_t r, uint32_t vo, uint32_t so, R, R) {
@@ -188,6 +190,8 @@ template <> struct Storage<ST_F64> {
 template <> struct Storage<ST_F32> {
     using T = float;
     using R = float;
+    __device__ static inline R dec(T v, R, R) { return v; }
+    __device__ static inline T enc(R v, R, R) { return v; }
     __device__ static inline R load(const T *p, R, R) { return __builtin_nontemporal_load(p); }
     __device__ static inline void store(T *p, R v, R, R) { __builtin_nontemporal_store(v, p); }
     __device__ static inline R ldb(rsrc_t r, uint32_t vo, uint32_t so, R, R) {
@@ -204,13 +208,14 @@ template <> struct Storage<ST_F32> {
 template <> struct Storage<ST_F16S> {
     using T = uint16_t;
     using R = float;
-    __device__ static inline R load(const T *p, R shift, R hsi) {
-        uint16_t bits = __builtin_nontemporal_load(p);
+    __device__ static inline R dec(T bits, R shift, R hsi) {
         return fmaf(__half2float(__ushort_as_half(bits)), hsi, shift);
     }
-    __device__ static inline void store(T *p, R v, R shs, R hs) {
-        __builtin_nontemporal_store(__half_as_ushort(__float2half_rn(fmaf(v, hs, -shs))), p);
+    __device__ static inline T enc(R v, R shs, R hs) {
+        return __half_as_ushort(__float2half_rn(fmaf(v, hs, -shs)));
     }
+    __device__ static inline R load(const T *p, R shift, R hsi) { return dec(__builtin_nontemporal_load(p), shift, hsi); }
+    __device__ static inline void store(T *p, R v, R shs, R hs) { __builtin_nontemporal_store(enc(v, shs, hs), p); }
     __device__ static inline R ldb(rsrc_t r, uint32_t vo, uint32_t so, R shift, R hsi) {
         const uint16_t bits = __builtin_amdgcn_raw_buffer_load_b16(r, (int)vo, (int)so, LBM_BUF_AUX);
         return fmaf(__half2float(__ushort_as_half(bits)), hsi, shift);
