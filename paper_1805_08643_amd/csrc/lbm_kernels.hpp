@@ -293,12 +293,24 @@ __device__ inline void lds_barrier() {
 // One block's z-march over a tile.  ps: LDS ring of 4 planes of
 // (ty + 2) x (tx + 2) psi values.
 //
-// Per plane z the block (i) pulls plane z+1 for its interior columns and its
-// halo ring, all loads in flight together; (ii) turns the densities into psi
-// in LDS; (iii) barriers; (iv) collides and stores plane z, whose
-// populations were pulled one iteration earlier and stayed in registers.
-// (Prefetching plane z+2 before the collision, for the whole tile or for the
-// halo only, measured slower on MI355X.)
+// Per plane z the block pulls plane z + 1 for its columns and its halo ring,
+// all loads in flight together, turns the densities into psi in LDS, barriers,
+// and collides and stores plane z, whose populations stayed in registers.
+// AHEAD: the loads of plane z + 2 are issued before plane z is collided and
+// waited for after it is stored.  That takes a third set of registers: 168
+// VGPRs, just three waves per SIMD, for the periodic non-orthogonal FP32
+// kernel, where it gains 3-7% (132 against 143 us at 150^3, 31.0 against 32.2
+// at 101 x 97 x 89); with walls, the orthogonal operator or F16S it needs more,
+// loses the third wave and measured slower (19.5 against 18.4 us on a walled
+// 75 x 61 x 43), and in FP64 it spills.
+//
+// Bound by the address unit at about 70% of the time the compute units are
+// busy (8.4 cycles per wave access: rows that do not start on 64 bytes take
+// every access in two halves), the rest being the march's latency.  Against
+// divergent branches, wrapping divisions and a register copy per plane it
+// measured (best tile of a sweep each) 5.8 against 6.4 us at 32^3 and 132
+// against 146 at 150^3 in FP32, 7.8 against 8.5 at 32^3 and 1118 against 1154 at
+// 256^3 in FP64.
 template <int S, int OP, bool WALL>
 __device__ inline void tile_march(const typename Storage<S>::T *__restrict__ A,
                                   typename Storage<S>::T *__restrict__ B,
@@ -307,6 +319,7 @@ __device__ inline void tile_march(const typename Storage<S>::T *__restrict__ A,
                                   typename Storage<S>::R *ps) {
     using ST = Storage<S>;
     using R = typename ST::R;
+    constexpr bool AHEAD = S == ST_F32 && OP == OP_NONORTH && !WALL;
     const int TX = g.tx, TY = g.ty;
     const int SX = TX + 2, SP = (TY + 2) * SX;
     int t = tile;
@@ -318,101 +331,160 @@ __device__ inline void tile_march(const typename Storage<S>::T *__restrict__ A,
     const int zb = izc * g.cz;
     const int ze = min(zb + g.cz, g.nz);
     const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const int w = min(TX, nx - x0), h = min(TY, ny - y0);  // the tile's nodes in x and y
     const size_t N = (size_t)g.N;
-    const int tid = threadIdx.x;
-
-    // Interior column of this thread.
-    const int lx = tid % TX, ly = tid / TX;
-    const bool inner = ly < TY;
-    const bool need_in = inner && lx <= nx - x0 && ly <= ny - y0;
-    const bool active = inner && x0 + lx < nx && y0 + ly < ny;
-    const int gx = wrapi(x0 + lx, nx), gy = wrapi(y0 + ly, ny);
-    const int cin = (ly + 1) * SX + lx + 1;
     constexpr uint32_t E = sizeof(typename ST::T);
     const uint32_t PB = (uint32_t)((size_t)nx * ny * E);  // bytes of one z-plane of one direction
     PopBuf bA, bB;
     bA.set(A, N);
     bB.set(B, N);
+
+    // Roles by wave (scalar branches): waves with interior columns, and waves
+    // with nodes of the halo ring, which is dealt from the last thread down so
+    // that threads without a column take it first.  Lanes beyond either set
+    // repeat its last node, so no load or store sits in a divergent branch
+    // and the waits for loads need not cover the stores.
+    const int tid = threadIdx.x, first = __builtin_amdgcn_readfirstlane(tid);
+    const int nh = 2 * (w + 2) + 2 * h;
+    const bool wave_in = first < TX * TY, wave_halo = (int)blockDim.x - 64 - first < nh;
+
+    // Interior column.
+    int ly = (int)(((float)tid + 0.5f) * __builtin_amdgcn_rcpf((float)TX)), lx = tid - ly * TX;
+    lx = min(lx, w - 1);
+    ly = min(ly, h - 1);
+    const int cin = (ly + 1) * SX + lx + 1;
+    auto up = [](int v, int n) { return v + 1 == n ? 0 : v + 1; };
+    auto down = [](int v, int n) { return v == 0 ? n - 1 : v - 1; };
     NbOff oin;
-    oin.set(gx, wrapi(gx - 1, nx), wrapi(gx + 1, nx), gy, wrapi(gy - 1, ny), wrapi(gy + 1, ny), nx, E);
+    oin.set(x0 + lx, down(x0 + lx, nx), up(x0 + lx, nx), y0 + ly, down(y0 + ly, ny), up(y0 + ly, ny), nx, E);
 
-    // Halo ring position of this thread (top row, bottom row, left, right).
-    const int nh = 2 * SX + 2 * TY;
-    int hlx = -1, hly = -1;
-    bool halo = false;
-    if (tid < nh) {
-        int h = tid;
-        if (h < SX) {
-            hlx = h - 1;
-            hly = -1;
-        } else if (h < 2 * SX) {
-            hlx = h - SX - 1;
-            hly = TY;
-        } else if (h < 2 * SX + TY) {
-            hlx = -1;
-            hly = h - 2 * SX;
-        } else {
-            hlx = TX;
-            hly = h - 2 * SX - TY;
-        }
-        halo = hlx <= nx - x0 && hly <= ny - y0;
-    }
-    const int hx = wrapi(x0 + hlx, nx), hy = wrapi(y0 + hly, ny);
-    const int chl = (hly + 1) * SX + hlx + 1;
+    // Halo ring position of this thread (bottom row, top row, left, right).
+    int hx, hy, chl;
     NbOff oh;
-    oh.set(hx, wrapi(hx - 1, nx), wrapi(hx + 1, nx), hy, wrapi(hy - 1, ny), wrapi(hy + 1, ny), nx, E);
+    {
+        const int k = min((int)blockDim.x - 1 - tid, nh - 1);
+        const int hlx = k < 2 * (w + 2) ? (k < w + 2 ? k - 1 : k - w - 3) : (k < 2 * (w + 2) + h ? -1 : w);
+        const int hly = k < w + 2 ? -1 : (k < 2 * (w + 2) ? h : (k < 2 * (w + 2) + h ? k - 2 * (w + 2) : k - 2 * (w + 2) - h));
+        chl = (hly + 1) * SX + hlx + 1;
+        hx = x0 + hlx;
+        hy = y0 + hly;
+        hx = hx < 0 ? nx - 1 : (hx == nx ? 0 : hx);
+        hy = hy < 0 ? ny - 1 : (hy == ny ? 0 : hy);
+        oh.set(hx, down(hx, nx), up(hx, nx), hy, down(hy, ny), up(hy, ny), nx, E);
+    }
 
-    R fc[Q], fn[Q], fh[Q];
-    R rc = (R)1, rn = (R)1;
-
-    // Issue the loads of plane zp (interior into fi, halo into fhh).
-    auto issue = [&](int zp, R *fi, R *fhh, bool do_in, bool do_halo) {
-        if (WALL && (zp < 0 || zp >= nz)) return;
-        const int zw = WALL ? zp : wrapi(zp, nz);
-        if (do_in && need_in) pull<S, WALL>(bA, nz, PB, zw, oin, P, fi);
-        if (do_halo && halo) pull<S, WALL>(bA, nz, PB, zw, oh, P, fhh);
-    };
-    // Densities and psi of plane zp into its LDS slot.
-    auto finish = [&](int zp, R *slot, const R *fi, const R *fhh, R &rk, bool do_in, bool do_halo) {
-        if (WALL && (zp < 0 || zp >= nz)) {
-            const R *gp = gpsi + (zp < 0 ? 0 : (size_t)nx * ny);
-            if (do_in && need_in) slot[cin] = gp[(size_t)gy * nx + gx];
-            if (do_halo && halo) slot[chl] = gp[(size_t)hy * nx + hx];
-            return;
-        }
-        if (do_in && need_in) {
-            rk = sum19<R>(fi);
-            slot[cin] = pseudo_psi<R>(P, rk);
-        }
-        if (do_halo && halo) slot[chl] = pseudo_psi<R>(P, sum19<R>(fhh));
-    };
     auto slot_of = [&](int z) { return ps + ((z - zb + 1) & 3) * SP; };
-
-    issue(zb - 1, fn, fh, true, true);
-    finish(zb - 1, slot_of(zb - 1), fn, fh, rn, true, true);
-    issue(zb, fc, fh, true, true);
-    finish(zb, slot_of(zb), fc, fh, rc, true, true);
-    for (int z = zb; z < ze; ++z) {
-        issue(z + 1, fn, fh, true, true);
-        finish(z + 1, slot_of(z + 1), fn, fh, rn, true, true);
-        lds_barrier();
-        if (active) {
-            R ax, ay, az;
-            const R *mid = slot_of(z);
-            psi_stencil<R>(slot_of(z - 1), mid, slot_of(z + 1), cin, SX, ax, ay, az);
-            const R mG_psi = -P.G * mid[cin];
-            const R Fx = mG_psi * ax + rc * P.gx;
-            const R Fy = mG_psi * ay + rc * P.gy;
-            const R Fz = mG_psi * az + rc * P.gz;
-            const R acc2 = ax * ax + ay * ay + az * az;
-            collide<R, OP>(fc, rc, Fx, Fy, Fz, acc2, P);
-            const uint32_t pz = (uint32_t)z * PB;
-#pragma unroll
-            for (int a = 0; a < Q; ++a) ST::stb(fc[a], bB.of(a), oin.c, bB.so(a, pz), P.shh(a), P.hs);
+    auto ghost = [&](int zp) { return WALL && (zp < 0 || zp >= nz); };  // beyond a wall: psi from gpsi
+    auto zwrap = [&](int zp) { return zp < 0 ? nz - 1 : (zp >= nz ? 0 : zp); };
+    auto load = [&](int zp, const NbOff &o, R *f) {
+        if (!ghost(zp)) pull<S, WALL>(bA, nz, PB, zwrap(zp), o, P, f);
+    };
+    // Density (returned) and psi of a plane's node into its LDS slot.
+    auto put = [&](int zp, int c, int x, int y, const R *f) {
+        R *slot = slot_of(zp);
+        if (ghost(zp)) {
+            slot[c] = gpsi[(zp < 0 ? 0 : (size_t)nx * ny) + (size_t)y * nx + x];
+            return (R)1;
         }
+        const R rho = sum19<R>(f);
+        slot[c] = pseudo_psi<R>(P, rho);
+        return rho;
+    };
+
+    if (!wave_in) {  // halo nodes only
+        R f[Q];
+        for (int z = zb - 1; z <= ze; ++z) {
+            if (wave_halo) {
+                load(z, oh, f);
+                put(z, chl, hx, hy, f);
+            }
+            if (z > zb) lds_barrier();
+        }
+        return;
+    }
+    auto collide_store = [&](int z, R *fc, R rc) {
+        R ax, ay, az;
+        const R *mid = slot_of(z);
+        psi_stencil<R>(slot_of(z - 1), mid, slot_of(z + 1), cin, SX, ax, ay, az);
+        const R mG_psi = -P.G * mid[cin];
+        const R Fx = mG_psi * ax + rc * P.gx;
+        const R Fy = mG_psi * ay + rc * P.gy;
+        const R Fz = mG_psi * az + rc * P.gz;
+        const R acc2 = ax * ax + ay * ay + az * az;
+        collide<R, OP>(fc, rc, Fx, Fy, Fz, acc2, P);
+        const uint32_t pz = (uint32_t)z * PB;
 #pragma unroll
-        for (int a = 0; a < Q; ++a) fc[a] = fn[a];
-        rc = rn;
+        for (int a = 0; a < Q; ++a) ST::stb(fc[a], bB.of(a), oin.c, bB.so(a, pz), P.shh(a), P.hs);
+    };
+    if constexpr (AHEAD) {
+        R f0[Q], f1[Q], f2[Q], fh[Q];
+        R r0, r1, r2;
+        load(zb - 1, oin, f2);
+        load(zb, oin, f0);
+        load(zb + 1, oin, f1);
+        if (wave_halo) {
+            R ha[Q], hb[Q];
+            load(zb - 1, oh, fh);
+            load(zb, oh, ha);
+            load(zb + 1, oh, hb);
+            put(zb - 1, chl, hx, hy, fh);
+            put(zb, chl, hx, hy, ha);
+            put(zb + 1, chl, hx, hy, hb);
+        }
+        put(zb - 1, cin, x0 + lx, y0 + ly, f2);
+        r0 = put(zb, cin, x0 + lx, y0 + ly, f0);
+        r1 = put(zb + 1, cin, x0 + lx, y0 + ly, f1);
+        lds_barrier();
+        auto body = [&](int z, R *fc, R rc, R *fp, R &rp) {
+            if (z + 2 <= ze) {
+                if (wave_halo) load(z + 2, oh, fh);
+                load(z + 2, oin, fp);
+            }
+            __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the collision
+            collide_store(z, fc, rc);
+            if (z + 2 <= ze) {
+                rp = put(z + 2, cin, x0 + lx, y0 + ly, fp);
+                if (wave_halo) put(z + 2, chl, hx, hy, fh);
+                lds_barrier();
+            }
+        };
+        for (int z = zb;;) {  // three planes in turn in three sets of registers
+            body(z, f0, r0, f2, r2);
+            if (++z == ze) break;
+            body(z, f1, r1, f0, r0);
+            if (++z == ze) break;
+            body(z, f2, r2, f1, r1);
+            if (++z == ze) break;
+        }
+    } else {
+        R f0[Q], f1[Q], fh[Q];
+        R r0, r1;
+        auto fetch = [&](int z, R *f) {
+            load(z, oin, f);
+            if (wave_halo) {
+                load(z, oh, fh);
+                put(z, chl, hx, hy, fh);
+            }
+            return put(z, cin, x0 + lx, y0 + ly, f);
+        };
+        fetch(zb - 1, f1);
+        r0 = fetch(zb, f0);
+        for (int z = zb;;) {
+            r1 = fetch(z + 1, f1);
+            lds_barrier();
+            collide_store(z, f0, r0);
+            if (++z == ze) break;
+            if constexpr (sizeof(R) == 8) {  // unrolled, the walled FP64 kernels spill
+#pragma unroll
+                for (int a = 0; a < Q; ++a) f0[a] = f1[a];
+                r0 = r1;
+            } else {  // two planes in turn in two sets of registers
+                r0 = fetch(z + 1, f0);
+                lds_barrier();
+                collide_store(z, f1, r1);
+                if (++z == ze) break;
+            }
+        }
     }
 }
 
