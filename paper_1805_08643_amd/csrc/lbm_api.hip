@@ -188,7 +188,7 @@ Layout layout_of(const lbm_params &p) {
     off += pops;
     L.psi = off;
     off += align_up(N * real_bytes(p.storage));
-    L.rho_w = off;
+    L.rho_w = off;  // four planes that nothing uses now: part of the documented workspace and scratch sizes
     off += align_up(4 * plane * real_bytes(p.storage));
     L.gpsi = off;
     off += align_up(2 * plane * real_bytes(p.storage));
@@ -374,14 +374,13 @@ struct lbm_ctx {
     hipStream_t cap = nullptr;                   // capture stream of the graphs
     hipGraphExec_t graphs[2] = {nullptr, nullptr};  // k steps from buffer parity 0 / 1
 
-    // Wall-plane densities and ghost psi (Eq. (57)) in a buffer of their own
+    // Ghost psi (Eq. (57)) in a buffer of its own
     // instead of the workspace: the allocation-free step (lbm_step_noalloc).
     unsigned char *wall_scratch = nullptr;
 
     void *state() const { return ws + (cur ? L.B : L.A); }
     void *other() const { return ws + (cur ? L.A : L.B); }
     void *psi() const { return ws + L.psi; }
-    void *rho_w() const { return wall_scratch ? wall_scratch : ws + L.rho_w; }
     void *gpsi() const { return wall_scratch ? wall_scratch + (L.gpsi - L.rho_w) : ws + L.gpsi; }
     double *partial() const { return reinterpret_cast<double *>(ws + L.partial); }
     double *dout() const { return reinterpret_cast<double *>(ws + L.dout); }
@@ -425,11 +424,9 @@ lbm_status launch_walls(lbm_ctx *c, const void *src) {
         using T = typename Storage<S.value>::T;
         using R = typename Storage<S.value>::R;
         if (!W.value) return LBM_OK;
-        const long long plane = (long long)c->p.nx * c->p.ny;
-        hipLaunchKernelGGL(k_wall_rho<S.value>, dim3(grid1d(4 * plane, 256, 1LL << 30)), dim3(256), 0, c->stream,
-                           (const T *)src, (R *)c->rho_w(), c->g, c->pd);
-        hipLaunchKernelGGL(k_ghost_psi<R>, dim3(grid1d(2 * plane, 256, 1LL << 30)), dim3(256), 0, c->stream,
-                           (const R *)c->rho_w(), (R *)c->gpsi(), c->g, c->pd);
+        const unsigned blocks = 2u * (unsigned)((c->p.nx + WALL_X - 1) / WALL_X) * (unsigned)((c->p.ny + WALL_Y - 1) / WALL_Y);
+        hipLaunchKernelGGL(k_ghost_psi<S.value>, dim3(blocks), dim3(WALL_THREADS), 0, c->stream, (const T *)src,
+                           (R *)c->gpsi(), c->g, c->pd);
         HIP_TRY(hipGetLastError());
         return LBM_OK;
     });

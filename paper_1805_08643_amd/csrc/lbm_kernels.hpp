@@ -1873,46 +1873,60 @@ __global__ void __launch_bounds__(256)
 }
 
 // ---------------------------------------------------------------------------
-// Wall support, Eq. (57): densities of the first two layers at each wall,
-// then ghost psi one layer beyond each wall.
-// rho_w planes: 0 -> z=0, 1 -> z=1, 2 -> z=nz-2, 3 -> z=nz-1.
+// Wall support, Eq. (57): ghost psi one layer beyond each wall, from the
+// densities of the first two fluid layers.
+//
+// A block takes WALL_X x WALL_Y nodes of one wall: its threads pull the second
+// layer at their own node and the first layer over the tile and its one-node
+// ring (two nodes for some threads), all loads in flight together, and the
+// densities of the first layer meet in LDS.  Bound by launch and load latency,
+// not by bytes: one launch instead of a density pass over four planes and a
+// ghost pass, which took 5.8 + 4.8 us in FP64 at 160 x 160 and 5.3 + 2.9 in
+// FP32 at 75 x 61.
 // ---------------------------------------------------------------------------
+constexpr int WALL_X = 32, WALL_Y = 4, WALL_THREADS = WALL_X * WALL_Y;
 template <int S>
-__global__ void k_wall_rho(const typename Storage<S>::T *__restrict__ A,
-                           typename Storage<S>::R *__restrict__ rho_w, GridDesc g, PhysD pd) {
+__global__ void __launch_bounds__(WALL_THREADS)
+    k_ghost_psi(const typename Storage<S>::T *__restrict__ A, typename Storage<S>::R *__restrict__ gpsi, GridDesc g,
+                PhysD pd) {
     using R = typename Storage<S>::R;
+    constexpr int SX = WALL_X + 2, EXT = SX * (WALL_Y + 2);
+    static_assert(EXT <= 2 * WALL_THREADS, "two first-layer nodes per thread");
+    __shared__ R l1[EXT];
     Phys<R> P;
     P.load(pd);
     const int nx = g.nx, ny = g.ny, nz = g.nz;
-    const long long plane = (long long)nx * ny;
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 4 * plane) return;
-    const int k = (int)(i / plane);
-    const int rem = (int)(i - (long long)k * plane);
-    const int x = rem % nx, y = rem / nx;
-    const int z = k == 0 ? 0 : (k == 1 ? 1 : (k == 2 ? nz - 2 : nz - 1));
-    rho_w[i] = density_at<S, true>(A, g, x, y, z, P);
-}
-
-template <class R>
-__global__ void k_ghost_psi(const R *__restrict__ rho_w, R *__restrict__ gpsi, GridDesc g, PhysD pd) {
-    Phys<R> P;
-    P.load(pd);
-    const int nx = g.nx, ny = g.ny;
-    const long long plane = (long long)nx * ny;
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 2 * plane) return;
-    const int side = (int)(i / plane);
-    const int rem = (int)(i - side * plane);
-    const int x = rem % nx, y = rem / nx;
-    const R *l1 = rho_w + (side == 0 ? 0 : 3) * plane;  // first fluid layer
-    const R *l2 = rho_w + (side == 0 ? 1 : 2) * plane;  // second fluid layer
-    const R dx = l1[(size_t)y * nx + wrapi(x + 1, nx)] - l1[(size_t)y * nx + wrapi(x - 1, nx)];
-    const R dy = l1[(size_t)wrapi(y + 1, ny) * nx + x] - l1[(size_t)wrapi(y - 1, ny) * nx + x];
+    const int bx = (nx + WALL_X - 1) / WALL_X, by = (ny + WALL_Y - 1) / WALL_Y;
+    const int side = blockIdx.x >= (unsigned)(bx * by);
+    const int b = blockIdx.x - side * bx * by;
+    const int x0 = b % bx * WALL_X, y0 = b / bx * WALL_Y;
+    const int z1 = side ? nz - 1 : 0, z2 = side ? nz - 2 : 1;
+    const int tid = threadIdx.x;
+    // Node k of the tile and its ring, clamped to the ring of the lattice and wrapped.
+    auto node = [&](int k, int &x, int &y) {
+        const int ky = k / SX;
+        x = min(x0 + k - ky * SX - 1, nx);
+        y = min(y0 + ky - 1, ny);
+        x = x < 0 ? nx - 1 : (x == nx ? 0 : x);
+        y = y < 0 ? ny - 1 : (y == ny ? 0 : y);
+    };
+    const int x = x0 + tid % WALL_X, y = y0 + tid / WALL_X;
+    int xa, ya, xb, yb;
+    node(tid, xa, ya);
+    node(min(tid + WALL_THREADS, EXT - 1), xb, yb);
+    const R rho2 = density_at<S, true>(A, g, min(x, nx - 1), min(y, ny - 1), z2, P);
+    const R rhoa = density_at<S, true>(A, g, xa, ya, z1, P);
+    const R rhob = density_at<S, true>(A, g, xb, yb, z1, P);
+    l1[tid] = rhoa;
+    if (tid + WALL_THREADS < EXT) l1[tid + WALL_THREADS] = rhob;
+    __syncthreads();
+    if (x >= nx || y >= ny) return;
+    const int c = (tid / WALL_X + 1) * SX + tid % WALL_X + 1;
+    const R dx = l1[c + 1] - l1[c - 1], dy = l1[c + SX] - l1[c - SX];
     const R phi = r_sqrt(dx * dx + dy * dy);
-    R rg = l2[rem] + phi * P.tan_wall;
+    R rg = rho2 + phi * P.tan_wall;
     if (rg < P.ghost_rho_min) rg = P.ghost_rho_min;
-    gpsi[i] = pseudo_psi<R>(P, rg);
+    gpsi[((size_t)side * ny + y) * nx + x] = pseudo_psi<R>(P, rg);
 }
 
 // ---------------------------------------------------------------------------
