@@ -236,14 +236,8 @@ template <> struct Storage<ST_F16S> {
 // only the shift (w_a rt(x) instead of w_a rho_ref) changes from node to node.
 template <> struct Storage<ST_F16N> : Storage<ST_F16S> {};
 
-// F16N reference density: binary16 bits of a density, and back.  The FP32
-// density is opaque to the conversion: fused with the multiply-add that formed
-// it, it would be rounded once instead of twice and differ from the density
-// that the collision and the readback kernels use.
-__device__ inline uint16_t nref_bits(float rho) {
-    asm("" : "+v"(rho));
-    return __half_as_ushort(__float2half_rn(rho));
-}
+// F16N reference density: binary16 bits of a density, and back.
+__device__ inline uint16_t nref_bits(float rho) { return __half_as_ushort(__float2half_rn(rho)); }
 __device__ inline float nref_val(uint16_t bits) { return __half2float(__ushort_as_half(bits)); }
 // Shifts w_a rt of the three velocity classes, one FP32 product each.
 struct NodeShift {

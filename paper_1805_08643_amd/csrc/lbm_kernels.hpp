@@ -954,18 +954,6 @@ template <> struct Out8<ST_F16N> {
         return (unsigned long long)w2[0][a] | ((unsigned long long)w2[1][a] << 32);
     }
 };
-struct Out8Rolled {  // for a loop over the nodes that is kept rolled (k at run time)
-    unsigned long long w[Q];
-    __device__ inline Out8Rolled() {
-#pragma unroll
-        for (int a = 0; a < Q; ++a) w[a] = 0;
-    }
-    __device__ inline void set_dithered(int k, int a, float v) {
-        w[a] |= (unsigned long long)(__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(v, 0.0f)) & 0xFFFFu)
-                << (16 * k);
-    }
-    __device__ inline unsigned long long word(int a) const { return w[a]; }
-};
 template <> struct Out8<ST_F32> {
     uint32_t lo[Q], hi[Q];
     __device__ inline void put(int k, int a, float v, const Phys<float> &) {
@@ -1531,12 +1519,12 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
         const bool bot = WALL && c == 0, top = WALL && c == nz - 1;
         // Unrolled.  F16N keeps the second pair of nodes behind the first (a
         // scheduling barrier), so that only one pair's values are live: 172-188
-        // VGPRs and no spills.  With the branch on the viscosity rule at every
-        // node, the compiler collects the LDS reads of all four nodes ahead of
-        // one block of arithmetic and spills, so that form stays rolled.
-        constexpr int KU = NREF && VISC < 0 ? 1 : NPT;
-        std::conditional_t<KU == 1, Out8Rolled, Out8<S>> out;
-#pragma unroll KU
+        // VGPRs and no spills in all its variants.  What made it spill, and the
+        // walled and orthogonal kernels run rolled, was the branch on the
+        // viscosity rule at every node: it collected the LDS reads of all four
+        // nodes ahead of one block of arithmetic.
+        Out8<S> out;
+#pragma unroll
         for (int k = 0; k < NPT; ++k) {
             R f[Q];
             if constexpr (!NREF) unpack8<S>(q, k, P, f);
@@ -1555,9 +1543,8 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
                 const R rt = ref_of(rw, k), drho = hv.sum19();
                 const R rts = rt * P.hs, rho = rts + drho, mGs = mG_psi * P.hs;
                 const uint32_t nh = sr_node(key, (uint32_t)c * plane_n + nbase + (uint32_t)k);
-                auto force = [&](R a, R gr) { return __builtin_fmaf(rho, gr, mGs * a); };
-                collide_from<R, OP, true, VISC>(hv, f, rho, force(ax, P.gx), force(ay, P.gy), force(az, P.gz),
-                                                ax * ax + ay * ay + az * az, P, drho, rts);
+                collide_from<R, OP, true, VISC>(hv, f, rho, mGs * ax + rho * P.gx, mGs * ay + rho * P.gy,
+                                                mGs * az + rho * P.gz, ax * ax + ay * ay + az * az, P, drho, rts);
 #pragma unroll
                 for (int a = 0; a < Q; ++a) {
                     const bool back = (ez(a) < 0 && bot) || (ez(a) > 0 && top);
@@ -1566,7 +1553,7 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
                     out.set_dithered(k, a, f16_dithered(__builtin_fmaf(P.wh(a), rt - nref_val(pl[pos]), f[a]),
                                                         sr_dither(nh, a)));
                 }
-                if (KU > 1 && k == 1) __builtin_amdgcn_sched_barrier(0);
+                if (k == 1) __builtin_amdgcn_sched_barrier(0);
             } else {
                 const R rho = L.rbuf[bs][nb + k];
                 collide<R, OP, VISC>(f, rho, mG_psi * ax + rho * P.gx, mG_psi * ay + rho * P.gy,
@@ -1606,11 +1593,11 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
         }
     } else {
         setup(false);
-        // F16N with one viscosity runs a loop without the branch on the
-        // viscosity rule at every node (see collide_plane).  FP32 and F16S keep
-        // the branch, as the other step kernels do: without it the compiler now
-        // and then contracts other products into additions, and their
-        // populations have to agree bit for bit.
+        // F16N: two loops, so that the choice of the viscosity rule does not
+        // split the colliders' straight-line code at every node (see
+        // collide_plane).  FP32 and F16S decide per node, as the other step
+        // kernels do: without the branch the compiler contracts other products
+        // into additions, and their populations have to agree bit for bit.
         auto loop = [&](auto visc) {
             for (int i = 0; i < iters; ++i) {
                 const int c = zb - 3 + i;
@@ -1624,9 +1611,9 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
                 lds_barrier();
             }
         };
-        if (!NREF || P.visc) loop(std::integral_constant<int, -1>{});
+        if constexpr (!NREF) loop(std::integral_constant<int, -1>{});
+        else if (P.visc) loop(std::integral_constant<int, 1>{});
         else loop(std::integral_constant<int, 0>{});
-
     }
 }
 
