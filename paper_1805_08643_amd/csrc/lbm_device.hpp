@@ -82,7 +82,6 @@ template <class R> struct Phys {
     R lid6[3];
     R w_eps, w_epsj, w_epsj2, w_xx;
     R whs[3];  // class weights times 2^h_exp (exact): F16N's stored shift rt w_a 2^e is rt * whs in one rounding
-    R ksig_eh, ksig_epsh;  // ksig_e and ksig_eps times 2^h_exp (exact): F16N collides in units of 2^-h_exp
     __device__ inline void load(const PhysD &d) {
         G = (R)d.G;
         a = (R)d.a;
@@ -117,8 +116,6 @@ template <class R> struct Phys {
         shs[0] = shift[0] * hs;
         shs[1] = shift[1] * hs;
         shs[2] = shift[2] * hs;
-        ksig_eh = ksig_e * hs;
-        ksig_epsh = ksig_eps * hs;
         whs[0] = (R)(1.0 / 3.0) * hs;
         whs[1] = (R)(1.0 / 18.0) * hs;
         whs[2] = (R)(1.0 / 36.0) * hs;
@@ -135,8 +132,8 @@ template <class R> struct Phys {
     // Rate of the stress rows at a node of density rho: s_nu, or with a
     // density-dependent viscosity 1 / (3 nu + 1/2) with nu linear in rho
     // between (vrhoV, nuV) and (vrhoV + 1/vinv, nuV + dnu), clamped.
-    __device__ inline R snu_at(R rho) const { return visc ? snu_of(rho) : s_nu; }
-    __device__ inline R snu_of(R rho) const {
+    __device__ inline R snu_at(R rho) const {
+        if (!visc) return s_nu;
         R t = (rho - vrhoV) * vinv;
         t = t < (R)0 ? (R)0 : (t > (R)1 ? (R)1 : t);
         return r_rcp((R)3 * (nuV + t * dnu) + (R)0.5);
@@ -422,36 +419,6 @@ template <class R> __device__ inline void inv_orth(const R m[Q], R o[Q]) {
     o[18] = cyz - sy + sz - pyz - my - mz;
 }
 
-// The populations of a node as the transforms read them: pair sums and
-// differences f_a +- f_{a+1} of opposite directions, and f_a + o.
-template <class R> struct Values {
-    const R *f;
-    __device__ inline R sum(int a) const { return f[a] + f[a + 1]; }
-    __device__ inline R dif(int a) const { return f[a] - f[a + 1]; }
-    __device__ inline R plus(int a, R o) const { return f[a] + o; }
-    __device__ inline R at(int a) const { return f[a]; }
-};
-// Stored halves of a node (element k of each direction's word), in units of
-// 2^-h_exp: a mixed-precision multiply-add by an opaque 1 (the compiler would
-// split it otherwise) adds straight from the halves, with the rounding of an
-// FP32 addition of the converted values and without the conversions.
-struct Halves {
-    const unsigned long long *w;
-    int k;
-    float one;
-    __device__ inline Halves(const unsigned long long *w_, int k_) : w(w_), k(k_), one(1.0f) { asm("" : "+s"(one)); }
-    __device__ inline float at(int a) const {
-        return (float)__builtin_bit_cast(_Float16, (uint16_t)(w[a] >> (16 * k)));
-    }
-    __device__ inline float sum(int a) const { return __builtin_fmaf(at(a), one, at(a + 1)); }
-    __device__ inline float dif(int a) const { return __builtin_fmaf(-at(a + 1), one, at(a)); }
-    __device__ inline float plus(int a, float o) const { return __builtin_fmaf(at(a), one, o); }
-    // In the association of Pre::rho.
-    __device__ inline float sum19() const {
-        return plus(0, sum(1)) + sum(3) + sum(5) + (sum(7) + sum(9)) + (sum(11) + sum(13)) + (sum(15) + sum(17));
-    }
-};
-
 // Partial sums shared by both forward transforms.
 template <class R> struct Pre {
     R a12, a34, a56;   // axis pair sums
@@ -459,17 +426,16 @@ template <class R> struct Pre {
     R s16, s17, s18;   // sums of the xy, xz, yz diagonal quartets
     R p7, p8, p9;      // (f7+f8)-(f9+f10), (f11+f12)-(f13+f14), (f15+f16)-(f17+f18)
     R c10, c11, c12, c13, c14, c15;  // e_x^2 e_y, e_x e_y^2, e_x^2 e_z, e_x e_z^2, e_y^2 e_z, e_y e_z^2
-    // f: Values<R> or Halves
-    template <class F> __device__ inline void build(const F &f) {
-        a12 = f.sum(1);
-        a34 = f.sum(3);
-        a56 = f.sum(5);
-        d12 = f.dif(1);
-        d34 = f.dif(3);
-        d56 = f.dif(5);
-        R u78 = f.sum(7), u910 = f.sum(9), v78 = f.dif(7), v910 = f.dif(9);
-        R u1112 = f.sum(11), u1314 = f.sum(13), v1112 = f.dif(11), v1314 = f.dif(13);
-        R u1516 = f.sum(15), u1718 = f.sum(17), v1516 = f.dif(15), v1718 = f.dif(17);
+    __device__ inline void build(const R f[Q]) {
+        a12 = f[1] + f[2];
+        a34 = f[3] + f[4];
+        a56 = f[5] + f[6];
+        d12 = f[1] - f[2];
+        d34 = f[3] - f[4];
+        d56 = f[5] - f[6];
+        R u78 = f[7] + f[8], u910 = f[9] + f[10], v78 = f[7] - f[8], v910 = f[9] - f[10];
+        R u1112 = f[11] + f[12], u1314 = f[13] + f[14], v1112 = f[11] - f[12], v1314 = f[13] - f[14];
+        R u1516 = f[15] + f[16], u1718 = f[17] + f[18], v1516 = f[15] - f[16], v1718 = f[17] - f[18];
         s16 = u78 + u910;
         s17 = u1112 + u1314;
         s18 = u1516 + u1718;
@@ -505,22 +471,21 @@ template <class R> struct Pre {
 // eps rows, zero elsewhere), so the rows that hold them take their differences
 // from drho instead of subtracting two numbers of the size of rho; the other
 // rows are unchanged, and the update g* = g + Minv (m* - m) keeps the form.
-// Everything is linear in f, rho and F apart from u, so DEV takes f, rho, drho,
-// rt and F (not acc2) in units of 2^-h_exp, the stored halves themselves: the
-// factor is a power of two, so every rounding is that of the unscaled values.
 // ---------------------------------------------------------------------------
-//
-// VISC: whether the viscosity depends on the density, decided outside (1, 0)
-// or here (-1).
-template <class R, int OP, bool DEV, int VISC, class F>
-__device__ inline void collide_from(const F &f, R out[Q], R rho, R Fx, R Fy, R Fz, R acc2, const Phys<R> &P,
-                                    R drho, R rt) {
+template <class R, int OP, bool DEV = false>
+__device__ inline void collide(R f[Q], R rho, R Fx, R Fy, R Fz, R acc2, const Phys<R> &P,
+                               R *uout = nullptr, R drho = (R)0, R rt = (R)0) {
     Pre<R> pr;
     pr.build(f);
     const R inv_rho = r_rcp(rho);
     const R ux = (pr.jx() + (R)0.5 * Fx) * inv_rho;
     const R uy = (pr.jy() + (R)0.5 * Fy) * inv_rho;
     const R uz = (pr.jz() + (R)0.5 * Fz) * inv_rho;
+    if (uout) {
+        uout[0] = ux;
+        uout[1] = uy;
+        uout[2] = uz;
+    }
     const R uxx = ux * ux, uyy = uy * uy, uzz = uz * uz, u2 = uxx + uyy + uzz;
     const R Fux = Fx * ux, Fuy = Fy * uy, Fuz = Fz * uz, Fu = Fux + Fuy + Fuz;
     const R third = (R)(1.0 / 3.0);
@@ -529,10 +494,7 @@ __device__ inline void collide_from(const F &f, R out[Q], R rho, R Fx, R Fy, R F
     dm[1] = Fx;
     dm[2] = Fy;
     dm[3] = Fz;
-    R snu = P.s_nu;
-    if constexpr (VISC < 0) snu = P.snu_at(DEV ? rho * P.hsi : rho);
-    if constexpr (VISC > 0) snu = P.snu_of(DEV ? rho * P.hsi : rho);
-    const R ksig_e = DEV ? P.ksig_eh : P.ksig_e, ksig_eps = DEV ? P.ksig_epsh : P.ksig_eps;
+    const R snu = P.snu_at(rho);
     if (OP == OP_NONORTH) {
         const R ce = (R)1 - (R)0.5 * P.s_e, cn = (R)1 - (R)0.5 * snu;
         const R cq = (R)1 - (R)0.5 * P.s_q, cp = (R)1 - (R)0.5 * P.s_pi;
@@ -540,7 +502,7 @@ __device__ inline void collide_from(const F &f, R out[Q], R rho, R Fx, R Fy, R F
         R m4 = pr.a12 + pr.a34 + pr.a56 + (R)2 * (pr.s16 + pr.s17 + pr.s18);
         R m5 = (R)2 * pr.a12 - pr.a34 - pr.a56 + pr.s16 + pr.s17 - (R)2 * pr.s18;
         R m6 = pr.a34 - pr.a56 + pr.s16 - pr.s17;
-        dm[4] = P.s_e * ((DEV ? drho : rho) + rho * u2 - m4) + ce * (R)2 * Fu + ksig_e * acc2;
+        dm[4] = P.s_e * ((DEV ? drho : rho) + rho * u2 - m4) + ce * (R)2 * Fu + P.ksig_e * acc2;
         dm[5] = snu * (rho * ((R)2 * uxx - uyy - uzz) - m5) + cn * (R)2 * ((R)2 * Fux - Fuy - Fuz);
         dm[6] = snu * (rho * (uyy - uzz) - m6) + cn * (R)2 * (Fuy - Fuz);
         dm[7] = snu * (rho * ux * uy - pr.p7) + cn * (Fx * uy + Fy * ux);
@@ -564,8 +526,7 @@ __device__ inline void collide_from(const F &f, R out[Q], R rho, R Fx, R Fy, R F
         R o[Q];
         inv_nonorth<R>(dm, o);
 #pragma unroll
-        for (int a = 0; a < Q; ++a)  // the diagonals' factor 1/4 contracts into the addition
-            out[a] = a <= 6 ? f.plus(a, o[a]) : f.at(a) + o[a];
+        for (int a = 0; a < Q; ++a) f[a] += o[a];
     } else {
         // Orthogonal model: m_eq = M_orth f_eq (textbook D3Q19 equilibrium),
         // S = M_orth G (Guo forcing), or with eps_eq and pi_eq from the
@@ -576,8 +537,8 @@ __device__ inline void collide_from(const F &f, R out[Q], R rho, R Fx, R Fy, R F
         const R cn = (R)1 - (R)0.5 * snu, cq = (R)1 - (R)0.5 * P.s_q;
         const R cp = (R)1 - (R)0.5 * P.s_pi;
         const R sumax = pr.a12 + pr.a34 + pr.a56, sumdg = pr.s16 + pr.s17 + pr.s18;
-        const R e = (R)(-30) * f.at(0) - (R)11 * sumax + (R)8 * sumdg;
-        const R eps = (R)12 * f.at(0) - (R)4 * sumax + sumdg;
+        const R e = (R)(-30) * f[0] - (R)11 * sumax + (R)8 * sumdg;
+        const R eps = (R)12 * f[0] - (R)4 * sumax + sumdg;
         const R qxm = (R)(-4) * pr.d12 + pr.c11 + pr.c13;
         const R qym = (R)(-4) * pr.d34 + pr.c10 + pr.c15;
         const R qzm = (R)(-4) * pr.d56 + pr.c12 + pr.c14;
@@ -593,8 +554,8 @@ __device__ inline void collide_from(const F &f, R out[Q], R rho, R Fx, R Fy, R F
         const R e_eq = DEV ? (R)(-11) * drho + (R)19 * rho * u2 : rho * ((R)(-11) + (R)19 * u2);
         const R eps_eq = DEV ? P.w_eps * drho + (P.w_eps - (R)3) * rt + P.w_epsj * rho * u2
                              : rho * (P.w_eps + P.w_epsj * u2);
-        dm[1] = P.s_e * (e_eq - e) + ce * (R)38 * Fu + (R)19 * ksig_e * acc2;
-        dm[2] = P.s_eps * (eps_eq - eps) + cE * P.w_epsj2 * Fu - (R)16 * ksig_eps * acc2;
+        dm[1] = P.s_e * (e_eq - e) + ce * (R)38 * Fu + (R)19 * P.ksig_e * acc2;
+        dm[2] = P.s_eps * (eps_eq - eps) + cE * P.w_epsj2 * Fu - (R)16 * P.ksig_eps * acc2;
         dm[3] = Fx;
         dm[4] = P.s_q * (-two3 * rho * ux - qxm) - cq * two3 * Fx;
         dm[5] = Fy;
@@ -614,14 +575,8 @@ __device__ inline void collide_from(const F &f, R out[Q], R rho, R Fx, R Fy, R F
         R o[Q];
         inv_orth<R>(dm, o);
 #pragma unroll
-        for (int a = 0; a < Q; ++a) out[a] = f.plus(a, o[a]);
+        for (int a = 0; a < Q; ++a) f[a] += o[a];
     }
-}
-
-// In place on a node's values.
-template <class R, int OP, int VISC = -1>
-__device__ inline void collide(R f[Q], R rho, R Fx, R Fy, R Fz, R acc2, const Phys<R> &P) {
-    collide_from<R, OP, false, VISC>(Values<R>{f}, f, rho, Fx, Fy, Fz, acc2, P, (R)0, (R)0);
 }
 
 // Equilibrium populations M^-1 m_eq(rho, u) of either operator.

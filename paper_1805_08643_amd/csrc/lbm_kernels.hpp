@@ -33,9 +33,10 @@ struct GridDesc {
     int wall_x, wall_y;    // single-phase walls in x and y (moving lid on y = ny - 1/2)
 };
 
-// Periodic wrap of a coordinate in [-1, n] (anything beyond goes to node 0,
-// for lanes of a ragged tile whose loads nobody uses).
-__device__ inline int wrapi(int v, int n) { return v < 0 ? n - 1 : (v >= n ? 0 : v); }
+__device__ inline int wrapi(int v, int n) {
+    int r = v % n;
+    return r < 0 ? r + n : r;
+}
 
 // Blocks are dealt to the 8 XCDs round-robin; give each XCD a contiguous run
 // of tiles so that tiles sharing halo rows share an L2.
@@ -164,29 +165,6 @@ __device__ inline void pull(const PopBuf &A, int nz, uint32_t PB, int z, const N
 #undef LBM_LD
 }
 
-// F16N: the density at the node of pull()'s offsets, from the stored halves.
-template <bool WALL>
-__device__ inline float pull_rho_n(const PopBuf &A, int nz, uint32_t PB, int z, const NbOff &o, const Phys<float> &P) {
-    const bool bot = WALL && z == 0, top = WALL && z == nz - 1;
-    const int zm = WALL ? (bot ? z : z - 1) : (z == 0 ? nz - 1 : z - 1);
-    const int zq = WALL ? (top ? z : z + 1) : (z == nz - 1 ? 0 : z + 1);
-    const uint32_t pc = (uint32_t)z * PB, pm = (uint32_t)zm * PB, pq = (uint32_t)zq * PB;
-    auto ld = [&](int d, uint32_t plane, uint32_t off) {
-        return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(A.of(d), (int)off, (int)A.so(d, plane), LBM_BUF_AUX);
-    };
-    unsigned long long h[Q];
-    const float rt = nref_val(ld(19, pc, o.c));
-    const uint32_t off[Q] = {o.c,  o.xm, o.xp, o.ym, o.yp, o.c,  o.c,  o.mm, o.pp, o.pm,
-                             o.mp, o.xm, o.xp, o.xm, o.xp, o.ym, o.yp, o.ym, o.yp};
-#pragma unroll
-    for (int a = 0; a < Q; ++a) {
-        const bool back = (ez(a) > 0 && bot) || (ez(a) < 0 && top);  // wave-uniform
-        if (back) h[a] = ld(opp(a), pc, o.c);
-        else h[a] = ld(a, ez(a) > 0 ? pm : ez(a) < 0 ? pq : pc, off[a]);
-    }
-    return __builtin_fmaf(Halves(h, 0).sum19(), P.hsi, rt);
-}
-
 // Where the population arriving at (x, y, z) in direction a is stored, with
 // walls on any axis: (idx, d) of A, and whether it reflected off the moving
 // face y = ny - 1/2 (then it carries lid_term(a) on top of the stored value).
@@ -248,7 +226,7 @@ __device__ inline void pull_at(const typename Storage<S>::T *__restrict__ A, con
 template <class R> __device__ inline R sum19(const R f[Q]) {
     // Same association as Pre::rho, so psi and the collision see one density.
     Pre<R> pr;
-    pr.build(Values<R>{f});
+    pr.build(f);
     return pr.rho(f[0]);
 }
 
@@ -941,18 +919,31 @@ template <> struct Out8<ST_F16S> {
                ((unsigned long long)__builtin_bit_cast(uint32_t, hi[a]) << 32);
     }
 };
-// F16N: values arrive dithered in FP32, node by node, and are truncated toward
-// zero to binary16 two nodes per instruction.
+// F16N: values arrive dithered in FP32 and are truncated toward zero to
+// binary16 (the stochastic rounding of the collider).  Out8<ST_F16N> keeps them
+// and truncates two nodes per instruction at the store, for a loop over the
+// group's nodes that the compiler unrolls (constant k); Out8Rolled truncates
+// each at once and shifts it into bits 16k of the direction's word, for a loop
+// kept rolled (k at run time).
 template <> struct Out8<ST_F16N> {
-    float y[Q];  // the even node's dithered values until its neighbour's come
-    uint32_t w2[2][Q];
-    __device__ inline void set_dithered(int k, int a, float v) {
-        if (k & 1) w2[k >> 1][a] = f16_trunc2(y[a], v);
-        else y[a] = v;
-    }
+    float y[Q][4];  // dithered FP32 values, truncated in pairs at the store
+    __device__ inline void clear() {}
+    __device__ inline void set_dithered(int k, int a, float v) { y[a][k] = v; }
     __device__ inline unsigned long long word(int a) const {
-        return (unsigned long long)w2[0][a] | ((unsigned long long)w2[1][a] << 32);
+        return (unsigned long long)f16_trunc2(y[a][0], y[a][1]) | ((unsigned long long)f16_trunc2(y[a][2], y[a][3]) << 32);
     }
+};
+struct Out8Rolled {
+    unsigned long long w[Q];
+    __device__ inline void clear() {
+#pragma unroll
+        for (int a = 0; a < Q; ++a) w[a] = 0;
+    }
+    __device__ inline void set_dithered(int k, int a, float v) {
+        w[a] |= (unsigned long long)(__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(v, 0.0f)) & 0xFFFFu)
+                << (16 * k);
+    }
+    __device__ inline unsigned long long word(int a) const { return w[a]; }
 };
 template <> struct Out8<ST_F32> {
     uint32_t lo[Q], hi[Q];
@@ -1099,7 +1090,12 @@ template <int S> __device__ inline void unpack8(const Wide8 &r, int k, const Phy
 #pragma unroll
     for (int a = 0; a < Q; ++a) f[a] = Lane8<S>::cvt(r.w[a], k, P.sh(a), P.hsi);
 }
-// F16N: reference density of node k of a group (plane 19 at the group).
+// F16N: node k's deviations g_a = h_a 2^-e from w_a rt (exact in FP32); rt
+// is element k of the group's reference word (plane 19 at the group).
+__device__ inline void unpack8n(const Wide8 &r, int k, const Phys<float> &P, float g[Q]) {
+#pragma unroll
+    for (int a = 0; a < Q; ++a) g[a] = Lane8<ST_F16N>::cvt(r.w[a], k, 0.0f, P.hsi);
+}
 __device__ inline float ref_of(unsigned long long rw, int k) { return nref_val((uint16_t)(rw >> (16 * k))); }
 
 // z-march of a tile with four nodes per thread: tx nodes (a multiple of 4)
@@ -1280,15 +1276,13 @@ template <int S> struct SplitLds {
 // F16N adds a ring of this step's binary16 densities (with the halo): the
 // references of the populations the colliders store, each for the node that
 // will pull it.  To stay within the 160 KiB of LDS its tiles are smaller,
-// (tx + 2)(ty + 2) <= 1300 (128 x 8 nodes at most).  The references of the
-// populations in qbuf travel beside them; their densities do not, as the
-// colliders form the pair sums anyway.  (Loading the references from HBM
-// instead, a plane ahead, made the colliders wait for that load and, as the
-// vector-memory counter is in order, for the stores of a whole plane before
-// each barrier.)  154,080 bytes.
+// (tx + 2)(ty + 2) <= 1300 (128 x 8 nodes at most), and the colliders load
+// the reference word of their own group (the references of the populations
+// in qbuf) from HBM, where the pullers read it two planes earlier: 160,224 bytes.
 constexpr int SPLIT_SP_N = 1300;
 template <> struct SplitLds<ST_F16N> {
-    unsigned long long qbuf[3][Q + 1][SPLIT_ROLE];  // plane 19: the groups' reference words
+    unsigned long long qbuf[3][Q][SPLIT_ROLE];
+    float rbuf[3][SPLIT_NODES];
     float ring[4][SPLIT_SP_N];
     uint16_t nring[4][SPLIT_SP_N];  // binary16 densities of this step, slots as the psi ring
 };
@@ -1445,10 +1439,12 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
 #pragma unroll
         for (int r = 0; r < HR; ++r) {
             if (halo[r]) {
-                [[maybe_unused]] R fh[Q];
+                R fh[Q];
                 R rh;
                 if constexpr (NREF) {
-                    rh = pull_rho_n<WALL>(bA, nz, PB, pw, oh[r], P);
+                    float rth;
+                    pull<S, WALL, true>(bA, nz, PB, pw, oh[r], P, fh, &rth);
+                    rh = rth + sum19<R>(fh);
                     nsl[chl[r]] = nref_bits(rh);
                 } else {
                     pull<S, WALL>(bA, nz, PB, pw, oh[r], P, fh);
@@ -1462,16 +1458,17 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
         if (active) {
 #pragma unroll
             for (int a = 0; a < Q; ++a) qbuf[bs][a][rid] = q.w[a];
-            if constexpr (NREF) qbuf[bs][Q][rid] = rw;
         }
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
             R f[Q];
             R rho;
-            if constexpr (NREF) {
-                const R drho = Halves(q.w, k).sum19();
-                rho = __builtin_fmaf(drho, P.hsi, ref_of(rw, k));
+            if constexpr (NREF) {  // deviations; the density is rt + their sum, and rbuf keeps the sum
+                unpack8n(q, k, P, f);
+                const R drho = sum19<R>(f);
+                rho = ref_of(rw, k) + drho;
                 if (need_in) nsl[cin + k] = nref_bits(rho);
+                if (active) L.rbuf[bs][nb + k] = drho;
             } else {
                 unpack8<S>(q, k, P, f);
                 rho = sum19<R>(f);
@@ -1488,10 +1485,12 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
             if (halo[r]) slot[chl[r]] = gp[(size_t)hys[r] * nx + hxs[r]];
             return;
         }
-        [[maybe_unused]] R fh[Q];
+        R fh[Q];
         R rh;
         if constexpr (NREF) {
-            rh = pull_rho_n<WALL>(bA, nz, PB, zwrap(p), oh[r], P);
+            float rth;
+            pull<S, WALL, true>(bA, nz, PB, zwrap(p), oh[r], P, fh, &rth);
+            rh = rth + sum19<R>(fh);
         } else {
             pull<S, WALL>(bA, nz, PB, zwrap(p), oh[r], P, fh);
             rh = sum19<R>(fh);
@@ -1502,62 +1501,70 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
             if constexpr (NREF) nslot(p)[chl[r]] = nref_bits(rh);
         }
     };
-    // Collider: plane c from the LDS buffers to B.
-    auto collide_plane = [&](int c, auto visc) {
+    // F16N: reference word of the group at plane c in A (the colliders'
+    // copy of what the pullers read).
+    auto ref_word = [&](int c) -> unsigned long long {
+        return __builtin_bit_cast(unsigned long long,
+                                  __builtin_amdgcn_raw_buffer_load_b64(
+                                      bA.of(19), (int)oin.c,
+                                      (int)u_so(bA, 19, __builtin_amdgcn_readfirstlane((uint32_t)c * PB)),
+                                      LBM_BUF_AUX));
+    };
+    // Collider: plane c from the LDS buffers to B (rw: F16N reference word).
+    auto collide_plane = [&](int c, unsigned long long rw) {
         if (!active) return;
-        constexpr int VISC = decltype(visc)::value;
         const int bs = bslot(c);
         Wide8 q;
 #pragma unroll
         for (int a = 0; a < Q; ++a) q.w[a] = qbuf[bs][a][rid];
-        unsigned long long rw = 0;
-        if constexpr (NREF) rw = qbuf[bs][Q][rid];
         const R *lo = rslot(c - 1), *mid = rslot(c), *hi = rslot(c + 1);
         // F16N: this step's references of the planes below, at and above
         // (a population leaving through a wall comes back to its own node).
         const uint16_t *nlo = nslot(c - 1), *nmid = nslot(c), *nhi = nslot(c + 1);
         const bool bot = WALL && c == 0, top = WALL && c == nz - 1;
-        // Unrolled.  F16N keeps the second pair of nodes behind the first (a
-        // scheduling barrier), so that only one pair's values are live: 172-188
-        // VGPRs and no spills in all its variants.  What made it spill, and the
-        // walled and orthogonal kernels run rolled, was the branch on the
-        // viscosity rule at every node: it collected the LDS reads of all four
-        // nodes ahead of one block of arithmetic.
-        Out8<S> out;
-#pragma unroll
+        // The walled and orthogonal F16N kernels keep this loop rolled: one
+        // node's values live at a time.  Fully unrolled they spill into the loop
+        // over planes, where a spill reload also waits for the previous plane's
+        // stores (the vector-memory counter counts stores too), and the walled
+        // step took 1.09 ms instead of 0.83 ms on the 384 x 384 x 192 sessile
+        // lattice; unrolled by two (no reload in that loop) it took 1.04 ms.  The
+        // periodic non-orthogonal kernel unrolls without spilling, and rolled it
+        // measured 0.57 ms instead of 0.34 ms at 256^3.
+        constexpr int KU = (NREF && (WALL || OP == OP_ORTH)) ? 1 : NPT;
+        std::conditional_t<KU == 1, Out8Rolled, Out8<S>> out;
+        if constexpr (NREF) out.clear();
+#pragma unroll KU
         for (int k = 0; k < NPT; ++k) {
             R f[Q];
-            if constexpr (!NREF) unpack8<S>(q, k, P, f);
+            if constexpr (NREF) unpack8n(q, k, P, f);
+            else unpack8<S>(q, k, P, f);
             R ax, ay, az;
             psi_stencil<R>(lo, mid, hi, cin + k, SX, ax, ay, az);
             const R mG_psi = -P.G * mid[cin + k];
             if constexpr (NREF) {
                 // Deviations g from w_a rt (rt: the reference they were stored
-                // against) in units of 2^-e, collided in that form; a value for
-                // node x' is stored as g*_a + w_a (rt - rt'(x')) 2^e, rt' this
-                // step's reference of x' (the node itself where the value comes
-                // back from a wall), rounded stochastically with the dither of
-                // this node and a.  The difference of two binary16 references is
-                // exact in FP32.
-                const Halves hv(q.w, k);
-                const R rt = ref_of(rw, k), drho = hv.sum19();
-                const R rts = rt * P.hs, rho = rts + drho, mGs = mG_psi * P.hs;
+                // against), collided in that form; a value for node x' is stored
+                // as (g*_a + w_a (rt - rt'(x'))) 2^e, rt' this step's reference of
+                // x' (the node itself where the value comes back from a wall),
+                // rounded stochastically with the dither of this node and a.
+                // The difference of two binary16 references is exact in FP32.
+                const R rt = ref_of(rw, k), drho = L.rbuf[bs][nb + k];
+                const R rho = rt + drho;
                 const uint32_t nh = sr_node(key, (uint32_t)c * plane_n + nbase + (uint32_t)k);
-                collide_from<R, OP, true, VISC>(hv, f, rho, mGs * ax + rho * P.gx, mGs * ay + rho * P.gy,
-                                                mGs * az + rho * P.gz, ax * ax + ay * ay + az * az, P, drho, rts);
+                collide<R, OP, true>(f, rho, mG_psi * ax + rho * P.gx, mG_psi * ay + rho * P.gy,
+                                     mG_psi * az + rho * P.gz, ax * ax + ay * ay + az * az, P, nullptr, drho, rt);
 #pragma unroll
                 for (int a = 0; a < Q; ++a) {
                     const bool back = (ez(a) < 0 && bot) || (ez(a) > 0 && top);
                     const uint16_t *pl = back ? nmid : (ez(a) < 0 ? nlo : (ez(a) > 0 ? nhi : nmid));
                     const int pos = back ? cin + k : cin + k + ex(a) + ey(a) * SX;
-                    out.set_dithered(k, a, f16_dithered(__builtin_fmaf(P.wh(a), rt - nref_val(pl[pos]), f[a]),
+                    out.set_dithered(k, a, f16_dithered(__builtin_fmaf(P.wh(a), rt - nref_val(pl[pos]), f[a] * P.hs),
                                                         sr_dither(nh, a)));
                 }
-                if (k == 1) __builtin_amdgcn_sched_barrier(0);
             } else {
                 const R rho = L.rbuf[bs][nb + k];
-                collide<R, OP, VISC>(f, rho, mG_psi * ax + rho * P.gx, mG_psi * ay + rho * P.gy,
-                                     mG_psi * az + rho * P.gz, ax * ax + ay * ay + az * az, P);
+                collide<R, OP>(f, rho, mG_psi * ax + rho * P.gx, mG_psi * ay + rho * P.gy, mG_psi * az + rho * P.gz,
+                               ax * ax + ay * ay + az * az, P);
 #pragma unroll
                 for (int a = 0; a < Q; ++a) out.put(k, a, f[a], P);
             }
@@ -1593,27 +1600,24 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
         }
     } else {
         setup(false);
-        // F16N: two loops, so that the choice of the viscosity rule does not
-        // split the colliders' straight-line code at every node (see
-        // collide_plane).  FP32 and F16S decide per node, as the other step
-        // kernels do: without the branch the compiler contracts other products
-        // into additions, and their populations have to agree bit for bit.
-        auto loop = [&](auto visc) {
-            for (int i = 0; i < iters; ++i) {
-                const int c = zb - 3 + i;
-                if (c >= zb) collide_plane(c, visc);
-                if constexpr (RING2) {
-                    if (chw && c + 2 <= ze) halo_plane(c + 2, 0);
-                    if constexpr (CR > 1) {
-                        if (chw2 && c + 2 <= ze) halo_plane(c + 2, 1);
-                    }
-                }
-                lds_barrier();
+        unsigned long long rw_next = 0;
+        for (int i = 0; i < iters; ++i) {
+            const int c = zb - 3 + i;
+            // F16N: the next plane's reference word, issued a plane ahead and
+            // before this plane's stores.
+            const unsigned long long rw = rw_next;
+            if constexpr (NREF) {
+                if (c + 1 >= zb && c + 1 < ze) rw_next = ref_word(c + 1);
             }
-        };
-        if constexpr (!NREF) loop(std::integral_constant<int, -1>{});
-        else if (P.visc) loop(std::integral_constant<int, 1>{});
-        else loop(std::integral_constant<int, 0>{});
+            if (c >= zb) collide_plane(c, rw);
+            if constexpr (RING2) {
+                if (chw && c + 2 <= ze) halo_plane(c + 2, 0);
+                if constexpr (CR > 1) {
+                    if (chw2 && c + 2 <= ze) halo_plane(c + 2, 1);
+                }
+            }
+            lds_barrier();
+        }
     }
 }
 
@@ -1961,7 +1965,7 @@ __device__ inline void node_macro(const typename Storage<S>::T *__restrict__ A,
 #pragma unroll
     for (int a = 0; a < Q; ++a) finite = finite && isfinite(f[a]);
     Pre<R> pr;
-    pr.build(Values<R>{f});
+    pr.build(f);
     if constexpr (S == ST_F16N) rho = rt + pr.rho(f[0]);
     else rho = pr.rho(f[0]);
     j[0] = pr.jx();
