@@ -33,10 +33,11 @@ struct GridDesc {
     int wall_x, wall_y;    // single-phase walls in x and y (moving lid on y = ny - 1/2)
 };
 
-__device__ inline int wrapi(int v, int n) {
-    int r = v % n;
-    return r < 0 ? r + n : r;
-}
+// Periodic wrap of a coordinate in [-1, n] (anything beyond goes to node 0,
+// for lanes of a ragged tile whose loads nobody uses).  By division, wrapping
+// took more instructions than pulling a node: in a tile's setup, which short z
+// runs do not amortise, and 54 times per node in the readback kernels.
+__device__ inline int wrapi(int v, int n) { return v < 0 ? n - 1 : (v >= n ? 0 : v); }
 
 // Blocks are dealt to the 8 XCDs round-robin; give each XCD a contiguous run
 // of tiles so that tiles sharing halo rows share an L2.
@@ -1300,6 +1301,21 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
     using T = typename Storage<S>::T;
     constexpr int NPT = Lane8<S>::NPT;
     constexpr bool NREF = S == ST_F16N;
+    // F16N: whether the colliders leave a plane's stores in flight (see their
+    // loop).  The walled and orthogonal kernels gain 5-31%; the periodic
+    // non-orthogonal one loses (406 against 341 us at 256^3), and so it does
+    // with the wrap of wrapi, which lets its pullers issue their loads sooner:
+    // waiting for the stores first is what it does best with, measured and not
+    // explained.
+    constexpr bool AFLOAT = NREF && (WALL || OP == OP_ORTH);
+    auto wrap = [](int v, int n) {
+        if constexpr (NREF && !AFLOAT) {
+            const int r = v % n;
+            return r < 0 ? r + n : r;
+        } else {
+            return wrapi(v, n);
+        }
+    };
     auto &qbuf = L.qbuf;
     auto &ring = L.ring;
     const int TX = g.tx, TY = g.ty, TXG = g.tx / NPT;
@@ -1330,12 +1346,17 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
     // This thread's group (either role): nodes x0 + NPT lx .. + NPT - 1 of row
     // ly.  A group starting at nx (a ragged last tile) supplies psi of the
     // wrapped columns to the last real column.
-    const int lx = rid % TXG, ly = rid / TXG;
+    int lx = rid % TXG, ly = rid / TXG;
+    if (AFLOAT && !puller) {  // lanes without a group repeat the tile's last one (see the colliders' loop)
+        lx = min(lx, (min(TX, nx - x0) - 1) / NPT);
+        ly = min(ly, min(TY, ny - y0) - 1);
+    }
     const bool inner = ly < TY;
     const int xa = x0 + NPT * lx;
     const bool need_in = inner && xa <= nx && ly <= ny - y0;
     const bool active = inner && xa < nx && y0 + ly < ny;
-    const int gx = xa >= nx ? xa - nx : xa, gy = wrapi(y0 + (inner ? ly : 0), ny);
+    const int slot_q = AFLOAT && !puller ? ly * TXG + lx : rid;  // the group's slot in qbuf
+    const int gx = xa >= nx ? xa - nx : xa, gy = wrap(y0 + (inner ? ly : 0), ny);
     const bool wl = gx == 0, wr = gx + NPT - 1 == nx - 1;
     const int cin = (ly + 1) * SX + NPT * lx + 1;
     const int nb = ly * TX + NPT * lx;  // first node slot in rbuf
@@ -1364,7 +1385,7 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
     bool halo[2];
     NbOff oh[2];
     auto setup = [&](const bool pull_role) {
-    oin.set(gx, wl, wr, gy, wrapi(gy - 1, ny), wrapi(gy + 1, ny), nx);
+    oin.set(gx, wl, wr, gy, wrap(gy - 1, ny), wrap(gy + 1, ny), nx);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const int h = pull_role ? rid + r * SPLIT_ROLE : rid + (r + 1) * SPLIT_ROLE;
@@ -1386,17 +1407,17 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
             }
             halo[r] = hlx <= nx - x0 && hly <= ny - y0;
         }
-        hxs[r] = wrapi(x0 + hlx, nx);
-        hys[r] = wrapi(y0 + hly, ny);
+        hxs[r] = wrap(x0 + hlx, nx);
+        hys[r] = wrap(y0 + hly, ny);
         chl[r] = (hly + 1) * SX + hlx + 1;
-        oh[r].set(hxs[r], wrapi(hxs[r] - 1, nx), wrapi(hxs[r] + 1, nx), hys[r], wrapi(hys[r] - 1, ny),
-                  wrapi(hys[r] + 1, ny), nx, E);
+        oh[r].set(hxs[r], wrap(hxs[r] - 1, nx), wrap(hxs[r] + 1, nx), hys[r], wrap(hys[r] - 1, ny),
+                  wrap(hys[r] + 1, ny), nx, E);
     }
     };
     // Colliding waves with a halo node in the first / second round (wave-uniform).
     const bool chw = RING2 && !puller && (int)__builtin_amdgcn_readfirstlane(rid) + SPLIT_ROLE < nh;
     const bool chw2 = RING2 && CR > 1 && !puller && (int)__builtin_amdgcn_readfirstlane(rid) + 2 * SPLIT_ROLE < nh;
-    auto zwrap = [&](int zp) { return WALL ? zp : wrapi(zp, nz); };
+    auto zwrap = [&](int zp) { return WALL ? zp : wrap(zp, nz); };
     auto rslot = [&](int z) { return ring[(z - zb + 1) & 3]; };
     auto nslot = [&](int z) -> uint16_t * {
         if constexpr (NREF) return L.nring[(z - zb + 1) & 3];
@@ -1512,11 +1533,11 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
     };
     // Collider: plane c from the LDS buffers to B (rw: F16N reference word).
     auto collide_plane = [&](int c, unsigned long long rw) {
-        if (!active) return;
+        if (!AFLOAT && !active) return;
         const int bs = bslot(c);
         Wide8 q;
 #pragma unroll
-        for (int a = 0; a < Q; ++a) q.w[a] = qbuf[bs][a][rid];
+        for (int a = 0; a < Q; ++a) q.w[a] = qbuf[bs][a][slot_q];
         const R *lo = rslot(c - 1), *mid = rslot(c), *hi = rslot(c + 1);
         // F16N: this step's references of the planes below, at and above
         // (a population leaving through a wall comes back to its own node).
@@ -1600,23 +1621,44 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
         }
     } else {
         setup(false);
-        unsigned long long rw_next = 0;
-        for (int i = 0; i < iters; ++i) {
-            const int c = zb - 3 + i;
-            // F16N: the next plane's reference word, issued a plane ahead and
-            // before this plane's stores.
-            const unsigned long long rw = rw_next;
-            if constexpr (NREF) {
-                if (c + 1 >= zb && c + 1 < ze) rw_next = ref_word(c + 1);
+        if constexpr (AFLOAT) {
+            // The next plane's reference word is issued before this plane is
+            // collided, and nothing here branches around the stores: lanes
+            // without a group repeat another's, and waves without one only keep
+            // the barriers.  The wait for the word, which is in order, then
+            // leaves the plane's 20 stores in flight; behind a branch it waited
+            // for all of them before every barrier.
+            for (int i = 0; i < 3; ++i) lds_barrier();  // the pullers' first planes
+            if ((int)__builtin_amdgcn_readfirstlane(rid) >= TXG * min(TY, ny - y0)) {
+                for (int c = zb; c < ze; ++c) lds_barrier();
+                return;
             }
-            if (c >= zb) collide_plane(c, rw);
-            if constexpr (RING2) {
-                if (chw && c + 2 <= ze) halo_plane(c + 2, 0);
-                if constexpr (CR > 1) {
-                    if (chw2 && c + 2 <= ze) halo_plane(c + 2, 1);
+            unsigned long long rw = ref_word(zb);
+            for (int c = zb; c < ze; ++c) {
+                const unsigned long long next = ref_word(min(c + 1, ze - 1));
+                collide_plane(c, rw);
+                rw = next;
+                lds_barrier();
+            }
+        } else {
+            unsigned long long rw_next = 0;
+            for (int i = 0; i < iters; ++i) {
+                const int c = zb - 3 + i;
+                // F16N: the next plane's reference word, issued a plane ahead and
+                // before this plane's stores.
+                const unsigned long long rw = rw_next;
+                if constexpr (NREF) {
+                    if (c + 1 >= zb && c + 1 < ze) rw_next = ref_word(c + 1);
                 }
+                if (c >= zb) collide_plane(c, rw);
+                if constexpr (RING2) {
+                    if (chw && c + 2 <= ze) halo_plane(c + 2, 0);
+                    if constexpr (CR > 1) {
+                        if (chw2 && c + 2 <= ze) halo_plane(c + 2, 1);
+                    }
+                }
+                lds_barrier();
             }
-            lds_barrier();
         }
     }
 }

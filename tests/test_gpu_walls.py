@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 def test_ghost_layer_tiles(shape, storage):
     from paper_1805_08643_amd.binding import Lattice
     nx, ny, nz = shape
-    cfg = li.params(nx, ny, nz, storage=storage, wall_z=1, theta_wall_deg=60.0, ghost_rho_min=0.02,
+    cfg = li.params(nx, ny, nz, storage=storage, wall_z=1, T_over_Tc=0.8, theta_wall_deg=60.0, ghost_rho_min=0.02,
                     gravity=(0.0, 0.0, -1e-5))
     rho, u = li.random_fields(nx, ny, nz, seed=11, rho_lo=0.15, rho_hi=0.2, umax=0.02)
     lat = Lattice(cfg)
