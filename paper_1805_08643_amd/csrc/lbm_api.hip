@@ -8,9 +8,11 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <map>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -217,8 +219,6 @@ int npt_of(int mode, int storage) {
 
 constexpr size_t kMaxStepLds = 65536;
 
-// The split kernel's LDS holds tiles of up to SPLIT_TX x SPLIT_TY nodes,
-// SPLIT_ROLE quads per role.
 // Rounds of 256 threads that a split tile's halo ring may take: the pullers'
 // and the colliders' (one for F16S groups of four, two for FP32 pairs).
 int split_rounds(int npt) { return npt == 4 ? 2 : 3; }
@@ -227,16 +227,20 @@ int split_rounds(int npt) { return npt == 4 ? 2 : 3; }
 // (F16N's LDS also holds a ring of reference densities, so its tiles are smaller).
 int split_sp(int storage) { return storage == ST_F16N ? SPLIT_SP_N : SPLIT_SP; }
 
-lbm_status check_split_tile(const lbm_tile &t, int npt, int storage) {
+bool split_tile_fits(const lbm_tile &t, int npt, int storage) {
     // The halo ring, 2 (tx + 2) + 2 ty nodes, takes at most split_rounds(npt)
     // rounds of 256 threads (pullers, then colliders once for F16S, twice for FP32).
-    const int ring_max = split_rounds(npt) * SPLIT_ROLE / 2 - 2;
-    const int sp = split_sp(storage);
-    if (t.tx < npt || t.ty < 1 || t.cz < 1 || t.tx % npt || t.tx > SPLIT_TX || (t.tx / npt) * t.ty > SPLIT_ROLE ||
-        t.tx * t.ty > SPLIT_NODES || (t.tx + 2) * (t.ty + 2) > sp || t.tx + t.ty > ring_max)
+    return t.tx >= npt && t.ty >= 1 && t.cz >= 1 && t.tx % npt == 0 && t.tx <= SPLIT_TX &&
+           (t.tx / npt) * t.ty <= SPLIT_ROLE && t.tx * t.ty <= SPLIT_NODES &&
+           (t.tx + 2) * (t.ty + 2) <= split_sp(storage) && t.tx + t.ty <= split_rounds(npt) * SPLIT_ROLE / 2 - 2;
+}
+
+lbm_status check_split_tile(const lbm_tile &t, int npt, int storage) {
+    if (!split_tile_fits(t, npt, storage))
         return fail(LBM_ERR_INVALID_ARG, "split mode needs a tile width that is a multiple of %d and at most %d, at "
                     "most %d groups of %d nodes, %d nodes, (tx + 2)(ty + 2) <= %d and tx + ty <= %d; got %d x %d x %d",
-                    npt, SPLIT_TX, SPLIT_ROLE, npt, SPLIT_NODES, sp, ring_max, t.tx, t.ty, t.cz);
+                    npt, SPLIT_TX, SPLIT_ROLE, npt, SPLIT_NODES, split_sp(storage),
+                    split_rounds(npt) * SPLIT_ROLE / 2 - 2, t.tx, t.ty, t.cz);
     return LBM_OK;
 }
 
@@ -254,6 +258,11 @@ bool split_ring2(int tx, int ty) { return 2 * (tx + 2) + 2 * ty > SPLIT_ROLE; }
 int split_rows(int tx, int npt, int storage) {
     return std::max(1, std::min({SPLIT_ROLE / (tx / npt), SPLIT_NODES / tx, split_sp(storage) / (tx + 2) - 2,
                                  split_rounds(npt) * SPLIT_ROLE / 2 - 2 - tx}));
+}
+
+bool step_tile_fits(const lbm_tile &t, int storage, int npt) {
+    return t.tx >= 1 && t.ty >= 1 && t.tx % npt == 0 && block_threads(t.tx, t.ty, npt) <= STEP_MAX_THREADS &&
+           4 * (size_t)(t.ty + 2) * (t.tx + 2) * real_bytes(storage) <= kMaxStepLds;
 }
 
 lbm_status check_tile(const lbm_tile &t, int storage, int npt = 1) {
@@ -287,42 +296,111 @@ void fill_grid(GridDesc &g, const lbm_params &p, const lbm_tile &t) {
     g.per_xcd = (g.ntiles + 7) / 8;
 }
 
-lbm_tile default_tile(int nx, int ny, int nz) {
-    lbm_tile t{};
-    // x extent: whole row when short, otherwise the candidate of 64 or 32
-    // that wastes fewest columns.
-    if (nx <= 64) {
-        t.tx = nx;
-    } else {
-        const int w64 = (nx + 63) / 64 * 64 - nx, w32 = (nx + 31) / 32 * 32 - nx;
-        t.tx = w64 <= w32 ? 64 : 32;
-    }
-    t.ty = std::max(1, std::min(ny, STEP_MAX_THREADS / t.tx));
-    while (t.ty > 1 && block_threads(t.tx, t.ty) > STEP_MAX_THREADS) --t.ty;
-    while (block_threads(t.tx, t.ty) > STEP_MAX_THREADS && t.tx > 1) t.tx /= 2;
-    const int ncol = ((nx + t.tx - 1) / t.tx) * ((ny + t.ty - 1) / t.ty);
-    const int want = 2048;  // ~8 blocks per CU
-    int nzc = std::max(1, (want + ncol - 1) / ncol);
-    int cz = std::max(1, (nz + nzc - 1) / nzc);
-    cz = std::max(cz, std::min(nz, 8));
-    t.cz = cz;
-    return t;
+// Estimated cost of a step with a tile: the third power of its time in
+// microseconds, launch apart.  A block marches cz + 2 planes; a plane takes it
+// a fixed time (barriers, the latency of its loads) and more for every wave of
+// interior and halo nodes on its CU, and blocks beyond one residency of the
+// chip wait (a last round that is nearly empty costs almost as much as a full
+// one).  Against that stands the traffic: the populations once in and once
+// out, with more read again the shorter a tile's columns, its z runs and the
+// pieces of rows that its waves take are (pieces that start and end inside
+// 128-byte lines most), at the rate of the last-level cache or of HBM, and
+// somewhat slower while CUs are idle.  The sum
+// of third powers is a smooth maximum of the two.
+//
+// The constants were fitted to measured times: 119 lattices from 24 to 384
+// nodes a side with some 200 tiles each, all storages, with and without walls,
+// one, two and four nodes per thread and the split step.  One set serves all
+// of them: its pick takes 1.00 to 1.03 times the best measured tile's time in
+// the geometric mean of each step; the tiles used before it, made for 256^3
+// and with runs of at least 8 planes, took 1.45 (FP32 split) to 3.3 times
+// (F16S pairs).
+double tile_cost(int nx, int ny, int nz, int npt, int storage, bool split, const lbm_tile &t) {
+    constexpr double START = 1.0, PLANE = 1.8, WAVE = 0.13, HALO = 0.5;  // us a block, a plane, a wave; a halo wave's part
+    constexpr double HBM = 3.4e6, CACHE = 5.8e6;                         // bytes per us
+    constexpr double TAIL = 0.8;                                         // cost of the empty part of a last round
+    constexpr double LINE = 0.3, WHOLE = 0.5;                            // of a line a piece read twice; of whole lines
+    constexpr double ROWS = 0.2, PLANES = 0.3;                           // of a row a column, of a plane a run read twice
+    const double per_simd = storage == ST_F64 || npt > 1 ? 2 : 3;        // waves a SIMD's registers hold
+    const double ntiles = std::ceil((double)nx / t.tx) * std::ceil((double)ny / t.ty) * std::ceil((double)nz / t.cz);
+    const double iw = (t.tx / npt * t.ty + 63) / 64, hw = (2 * (t.tx + 2) + 2 * t.ty + 63) / 64;
+    // Blocks of a CU; a block of five waves takes two of a SIMD's places.
+    const double resident = split ? 1.0 : std::max(1.0, std::floor(per_simd / std::ceil(std::max(iw, hw) / 4)));
+    const double per_xcd = std::ceil(ntiles / 8), x = per_xcd / (32 * resident);
+    const double rounds = x <= 1 ? 1.0 : x + TAIL * (std::ceil(x) - x);
+    const double k = std::min(resident, std::ceil(per_xcd / 32));
+    const double march = rounds * (START + (t.cz + 2) * (PLANE + WAVE * k * (iw + HALO * hw)));
+    const int size = storage == ST_F64 ? 8 : storage == ST_F32 ? 4 : 2;
+    const double pops = (double)nx * ny * nz * size * (storage == ST_F16N ? 20 : 19);
+    // A wave takes one row or parts of several: a piece starts with every row and with every wave.
+    const int per_row = t.tx / npt, n = per_row * t.ty;
+    const double pieces = t.ty + (n + 63) / 64 - (n + std::lcm(per_row, 64) - 1) / std::lcm(per_row, 64);
+    const double line = (t.tx * size % 128 ? LINE : LINE * WHOLE) * 128 * pieces / ((double)t.tx * t.ty * size);
+    const double bytes = pops * (1 + (1 + line) * (1 + PLANES / t.cz) * (1 + ROWS / t.ty));
+    const double busy = per_xcd / (32 * k * std::ceil(per_xcd / (32 * k)));
+    const double move = bytes / ((2 * pops > (double)kLlcBytes ? HBM : CACHE) * std::sqrt(std::sqrt(busy)));
+    return march * march * march + move * move * move;
 }
 
-// Default tile with npt = 2 or 4 nodes per thread: rows of up to 128
-// columns, up to 512 interior threads, and z runs long enough that there are
-// about as many tiles as compute units (measured fastest at 256^3: 128 x 8 x
-// 64 with pairs).
-lbm_tile wide_tile(int nx, int ny, int nz, int npt) {
-    lbm_tile t{};
-    t.tx = std::min(nx, 128);
-    t.tx = (t.tx + npt - 1) / npt * npt;
-    t.ty = std::max(1, std::min(ny, STEP_MAX_THREADS / std::max(1, t.tx / npt)));
-    while (t.ty > 1 && block_threads(t.tx, t.ty, npt) > STEP_MAX_THREADS) --t.ty;
-    const int ncol = ((nx + t.tx - 1) / t.tx) * ((ny + t.ty - 1) / t.ty);
-    const int nzc = std::max(1, (256 + ncol - 1) / ncol);
-    t.cz = std::max(std::min(nz, 8), (nz + nzc - 1) / nzc);
-    return t;
+// Default tile of a step that takes npt nodes per thread: the cheapest of the
+// tiles that cut x, y and z into equal parts (rows of 24 to 256 nodes, at least
+// a wave of threads where the lattice has it, at most 6000 tiles unless the
+// whole height is one run).  Measured against the rule before it, z runs for
+// 2048 tiles (one node per thread) or 256 (the others) of fixed rows, in us a
+// step: FP64 32^3 38 -> 7.8, FP64 160 x 160 x 120 250 -> 224, FP32 split 32^3
+// 22 -> 9.1, FP32 split 150^3 with walls 242 -> 139, FP32 split 384 x 384 x 192
+// with walls 1478 -> 1076, F16S pairs 150^3 with walls 248 -> 101, F16N split
+// 160 x 160 x 120 197 -> 82; 256^3 keeps its tile (490, 295 and 334 with FP32,
+// F16S and F16N).  Of 212 lattices one was slower by more than 2% (6%).
+lbm_tile search_tile(int nx, int ny, int nz, int npt, int storage, bool split) {
+    lbm_tile best{std::min(nx, 24) / npt * npt, 1, nz, 0};
+    double least = std::numeric_limits<double>::infinity();
+    auto cuts = [](int n, int part) { return (int)(((long long)n + part - 1) / part); };
+    // The largest part of an equal cut of n that is at most this one.
+    auto equal = [&](int n, int part) { return part > 0 ? cuts(n, cuts(n, part)) : 0; };
+    for (int w = equal(nx, std::min(nx, 256)); w >= std::min(nx, 24); w = equal(nx, w - 1)) {
+        lbm_tile t{};
+        t.tx = (w + npt - 1) / npt * npt;
+        bool tallest = true;
+        for (int h = equal(ny, std::min(ny, 512)); h >= 1; h = equal(ny, h - 1)) {
+            t.ty = h;
+            t.cz = 1;
+            if (split ? !split_tile_fits(t, npt, storage) : !step_tile_fits(t, storage, npt)) continue;
+            if (!tallest && t.tx / npt * t.ty < 60) break;
+            tallest = false;
+            const double cols = (double)cuts(nx, t.tx) * cuts(ny, h);
+            for (int d = nz; d >= 1; d = equal(nz, d - 1)) {
+                t.cz = d;
+                if (d < nz && cols * cuts(nz, d) > 6000) break;
+                const double cost = tile_cost(nx, ny, nz, npt, storage, split, t);
+                if (cost < least) {
+                    least = cost;
+                    best = t;
+                }
+            }
+        }
+    }
+    return best;
+}
+
+// search_tile takes up to 0.4 ms of host time, which a step without a context would
+// pay on every call, so each thread keeps its last answer; the tile follows
+// from the arguments alone.
+lbm_tile pick_tile(const lbm_params &p, int mode) {
+    struct Key {
+        int nx, ny, nz, npt, storage, split;
+        bool operator==(const Key &o) const {
+            return nx == o.nx && ny == o.ny && nz == o.nz && npt == o.npt && storage == o.storage && split == o.split;
+        }
+    };
+    static thread_local Key last{};
+    static thread_local lbm_tile tile{};
+    const Key key{p.nx, p.ny, p.nz, npt_of(mode, p.storage), p.storage, mode == LBM_STEP_SPLIT};
+    if (!(key == last)) {
+        tile = search_tile(key.nx, key.ny, key.nz, key.npt, key.storage, key.split);
+        last = key;
+    }
+    return tile;
 }
 
 bool box_walls(const lbm_params &p) { return p.wall_x || p.wall_y; }
@@ -333,19 +411,6 @@ bool quads_apply(const lbm_params &p) { return p.storage == ST_F16S && p.nx % 4 
 bool split_apply(const lbm_params &p) {
     return !box_walls(p) && (((p.storage == ST_F16S || p.storage == ST_F16N) && p.nx % 4 == 0) ||
                              (p.storage == ST_F32 && p.nx % 2 == 0));
-}
-
-// Default tile of the split mode: rows of up to 128 nodes, up to
-// SPLIT_ROLE groups, z runs for about as many tiles as compute units.
-constexpr int SPLIT_TX_DEFAULT = 128;
-lbm_tile split_tile(int nx, int ny, int nz, int npt, int storage) {
-    lbm_tile t{};
-    t.tx = std::min(SPLIT_TX_DEFAULT, (nx + npt - 1) / npt * npt);
-    t.ty = std::max(1, std::min({ny, SPLIT_TY, split_rows(t.tx, npt, storage)}));
-    const int ncol = ((nx + t.tx - 1) / t.tx) * ((ny + t.ty - 1) / t.ty);
-    const int nzc = std::max(1, (256 + ncol - 1) / ncol);
-    t.cz = std::max(std::min(nz, 8), (nz + nzc - 1) / nzc);
-    return t;
 }
 
 }  // namespace
@@ -609,14 +674,12 @@ void default_mode(lbm_ctx *c) {
     const lbm_params &p = c->p;
     if (split_apply(p)) {
         c->mode = LBM_STEP_SPLIT;
-        c->tile = split_tile(p.nx, p.ny, p.nz, npt_of(LBM_STEP_SPLIT, p.storage), p.storage);
     } else if (pairs_apply(p)) {
         c->mode = LBM_STEP_PAIRS;
-        c->tile = wide_tile(p.nx, p.ny, p.nz, 2);
     } else {
         c->mode = LBM_STEP_FUSED;
-        c->tile = default_tile(p.nx, p.ny, p.nz);
     }
+    c->tile = pick_tile(p, c->mode);
     fill_grid(c->g, p, c->tile);
 }
 
@@ -1032,10 +1095,7 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t trials, lbm_tile *best) {
     for (int tx : txs)
         for (int ty : tys)
             for (int cz : czs) add(std::min(tx, c->p.nx), ty, cz);
-    if (cand.empty())
-        cand.push_back(c->mode == LBM_STEP_SPLIT ? split_tile(c->p.nx, c->p.ny, c->p.nz, npt, c->p.storage)
-                       : npt > 1           ? wide_tile(c->p.nx, c->p.ny, c->p.nz, npt)
-                                           : default_tile(c->p.nx, c->p.ny, c->p.nz));
+    cand.push_back(pick_tile(c->p, c->mode));
     g_err.clear();
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
@@ -1092,14 +1152,14 @@ lbm_status lbm_set_step_mode(lbm_ctx *c, int32_t mode, int32_t slab_planes) {
     if (mode == LBM_STEP_SPLIT) {
         if (check_split_tile(c->tile, npt, c->p.storage) != LBM_OK) {
             g_err.clear();
-            c->tile = split_tile(c->p.nx, c->p.ny, c->p.nz, npt, c->p.storage);
+            c->tile = pick_tile(c->p, mode);
             fill_grid(c->g, c->p, c->tile);
         }
     } else if (check_tile(c->tile, c->p.storage, npt) != LBM_OK) {
         // The tile of the previous mode need not suit this one (a pair tile
         // 128 nodes wide needs 1024 threads at one node per thread).
         g_err.clear();
-        c->tile = npt > 1 ? wide_tile(c->p.nx, c->p.ny, c->p.nz, npt) : default_tile(c->p.nx, c->p.ny, c->p.nz);
+        c->tile = pick_tile(c->p, mode);
         fill_grid(c->g, c->p, c->tile);
     }
     c->mode = mode;
@@ -1206,7 +1266,7 @@ lbm_tile batch_tile(const lbm_params &p, int item_nodes, int mode) {
     lbm_tile t{};
     if (mode == LBM_STEP_SPLIT) {  // whole rows up to 128 nodes, as many rows as the LDS takes
         const int npt = npt_of(mode, p.storage);
-        t.tx = std::min(SPLIT_TX_DEFAULT, p.nx);
+        t.tx = std::min(p.nx, 128);
         t.ty = std::max(1, std::min(p.ny, split_rows(t.tx, npt, p.storage)));
         const int cols = t.tx * t.ty;
         t.cz = std::max(1, std::min(p.nz, (item_nodes + cols / 2) / cols));
@@ -1215,7 +1275,7 @@ lbm_tile batch_tile(const lbm_params &p, int item_nodes, int mode) {
     const bool pairs = mode == LBM_STEP_PAIRS;
     if (pairs) t.tx = std::min(p.nx, 128);
     else if (p.nx <= 128) t.tx = p.nx;
-    else t.tx = default_tile(p.nx, p.ny, p.nz).tx;
+    else t.tx = (p.nx + 63) / 64 * 64 <= (p.nx + 31) / 32 * 32 ? 64 : 32;  // whichever wastes fewer columns
     const int per_row = pairs ? t.tx / 2 : t.tx;
     t.ty = std::max(1, std::min(p.ny, STEP_MAX_THREADS / per_row));
     while (t.ty > 1 && block_threads(t.tx, t.ty, pairs ? 2 : 1) > STEP_MAX_THREADS) --t.ty;

@@ -1265,7 +1265,7 @@ __global__ void LBM_STEP_ATTR k_step4(const uint16_t *__restrict__ A, uint16_t *
 // populations fit in LDS.  Per-node arithmetic is that of the one-node
 // kernel: the same populations bit for bit.
 // ---------------------------------------------------------------------------
-constexpr int SPLIT_TX = 256, SPLIT_TY = 8, SPLIT_ROLE = 256;  // max tile width / default rows, threads per role
+constexpr int SPLIT_TX = 256, SPLIT_ROLE = 256;  // max tile width, threads per role
 constexpr int SPLIT_SP = 6 * (SPLIT_TX + 2);                    // psi ring slot: (tx + 2)(ty + 2) <= 256 x 4 + ring
 constexpr int SPLIT_NODES = 1024;                               // max nodes per tile plane
 
