@@ -383,24 +383,24 @@ lbm_tile search_tile(int nx, int ny, int nz, int npt, int storage, bool split) {
     return best;
 }
 
-// search_tile takes up to 0.4 ms of host time, which a step without a context would
-// pay on every call, so each thread keeps its last answer; the tile follows
-// from the arguments alone.
+// search_tile takes up to 0.4 ms of host time, which a step without a context
+// would pay on every call and a batch for every run, so each thread keeps its
+// last answers; the tile follows from the arguments alone.
 lbm_tile pick_tile(const lbm_params &p, int mode) {
-    struct Key {
+    struct Answer {
         int nx, ny, nz, npt, storage, split;
-        bool operator==(const Key &o) const {
-            return nx == o.nx && ny == o.ny && nz == o.nz && npt == o.npt && storage == o.storage && split == o.split;
-        }
+        lbm_tile tile;
     };
-    static thread_local Key last{};
-    static thread_local lbm_tile tile{};
-    const Key key{p.nx, p.ny, p.nz, npt_of(mode, p.storage), p.storage, mode == LBM_STEP_SPLIT};
-    if (!(key == last)) {
-        tile = search_tile(key.nx, key.ny, key.nz, key.npt, key.storage, key.split);
-        last = key;
-    }
-    return tile;
+    static thread_local Answer kept[8]{};
+    static thread_local int oldest = 0;
+    const int npt = npt_of(mode, p.storage), split = mode == LBM_STEP_SPLIT;
+    for (const Answer &k : kept)
+        if (k.nx == p.nx && k.ny == p.ny && k.nz == p.nz && k.npt == npt && k.storage == p.storage && k.split == split)
+            return k.tile;
+    const lbm_tile t = search_tile(p.nx, p.ny, p.nz, npt, p.storage, split);
+    kept[oldest] = {p.nx, p.ny, p.nz, npt, p.storage, split, t};
+    oldest = (oldest + 1) % 8;
+    return t;
 }
 
 bool box_walls(const lbm_params &p) { return p.wall_x || p.wall_y; }
@@ -1247,6 +1247,7 @@ struct lbm_batch {
     size_t smem = 0;
     int parity = 0;
     int item_nodes = 8192;
+    bool items_set = false;  // by the caller or the autotuner
     int mode = LBM_STEP_FUSED;  // LBM_STEP_FUSED, LBM_STEP_PAIRS or LBM_STEP_SPLIT
     bool ring2 = false;         // split: some run's tile has a halo ring beyond the pullers
     int store_policy = LBM_STORE_AUTO;
@@ -1306,6 +1307,44 @@ size_t batch_total(const lbm_params *runs, int32_t n, std::vector<size_t> *offs,
     if (desc_off) *desc_off = off;
     off += align_up(sizeof(RunDesc) * (size_t)n);
     return off;
+}
+
+// Default nodes per work item.  The split step's grid is one block per CU that
+// strides over the items, so a step ends with the block that has most to march:
+// the item size is the one whose most loaded block has least, an item costing
+// its columns times its planes and two more.  Many runs take long items (fewer
+// planes read twice), few runs short ones (no block idle).  Measured, us a step
+// with 8192 nodes for all and so: 64 runs of 32^3 to 96^3 525 -> 470 with F16S,
+// 606 -> 521 with F16N; 20 runs 145 -> 139 and 165 -> 153; 6 runs, and FP32,
+// keep 8192.  The other steps' items are within 2% of their best at 8192.
+int default_items(const lbm_batch *b) {
+    constexpr int ITEMS = 8192;
+    if (b->mode != LBM_STEP_SPLIT) return ITEMS;
+    int best = ITEMS;
+    long long least = std::numeric_limits<long long>::max();
+    for (int size : {8192, 4096, 12288, 16384, 24576, 32768}) {
+        long long n = 0;
+        GridDesc g{};
+        for (const lbm_ctx *c : b->runs) {
+            fill_grid(g, c->p, batch_tile(c->p, size, b->mode));
+            n += g.ntiles;
+        }
+        const long long blocks = std::min(n, 256ll), per_xcd = (n + 7) / 8;
+        long long load[256] = {}, item = 0;
+        for (const lbm_ctx *c : b->runs) {
+            fill_grid(g, c->p, batch_tile(c->p, size, b->mode));
+            for (int k = 0; k < g.nzc; ++k)
+                for (int t = 0; t < g.ntx * g.nty; ++t, ++item)  // xcd_tile's order, backwards
+                    load[(item % per_xcd * 8 + item / per_xcd) % blocks] +=
+                        (long long)g.tx * g.ty * (std::min(g.cz, g.nz - k * g.cz) + 2);
+        }
+        const long long most = *std::max_element(load, load + 256);
+        if (most < least) {
+            least = most;
+            best = size;
+        }
+    }
+    return best;
 }
 
 lbm_status batch_build(lbm_batch *b) {
@@ -1475,6 +1514,7 @@ lbm_status lbm_batch_create(const lbm_params *runs, int32_t n, void *dev_ws, siz
         }
         b->runs.push_back(c);
     }
+    b->item_nodes = default_items(b);
     if ((s = batch_build(b))) {
         lbm_batch_destroy(b);
         return s;
@@ -1617,6 +1657,7 @@ lbm_status lbm_batch_set_item_nodes(lbm_batch *b, int32_t item_nodes) {
     if (item_nodes < 1 || item_nodes > (1 << 24))
         return fail(LBM_ERR_INVALID_ARG, "item_nodes %d outside [1, 2^24]", item_nodes);
     b->item_nodes = item_nodes;
+    b->items_set = true;
     lbm_status s = batch_build(b);
     if (s) return s;
     b->blocks = std::min(b->blocks, b->total_tiles);
@@ -1647,6 +1688,7 @@ lbm_status lbm_batch_set_step_mode(lbm_batch *b, int32_t mode) {
         return fail(LBM_ERR_UNSUPPORTED, "split mode needs FP32 with even nx or F16S or F16N with nx a multiple of 4 in "
                     "every run");
     b->mode = mode;
+    if (!b->items_set) b->item_nodes = default_items(b);
     lbm_status s = batch_build(b);
     if (s) return s;
     b->blocks = std::min(mode == LBM_STEP_SPLIT ? 256 : b->blocks, b->total_tiles);
@@ -1716,6 +1758,7 @@ lbm_status lbm_batch_autotune(lbm_batch *b, int32_t trials, int32_t *best_blocks
     (void)hipEventDestroy(e1);
     b->mode = best_mode;
     b->item_nodes = best_items;
+    b->items_set = true;
     if ((s = batch_build(b))) return s;
     b->blocks = best_blk;
     if (best_blocks) *best_blocks = best_blk;

@@ -39,3 +39,29 @@ def test_default_tile(shape, storage):
         states.append(lat.read_populations().cpu().numpy())
         lat.close()
     assert np.array_equal(states[0], states[1])
+
+
+@pytest.mark.parametrize("storage,count", [("f16s", 2), ("f16s", 40), ("f32", 40)])
+def test_default_batch_items(storage, count):
+    """Few runs and many: the item size a batch chooses gives the states of
+    another one; a mode change chooses anew unless the caller had chosen."""
+    from paper_1805_08643_amd.binding import Batch
+    runs = li.c5_batch(n_runs=count, seed=3, sizes=(32, 48))
+    batches = []
+    for chosen in (False, True):
+        b = Batch([dict(p, storage=storage, rho_ref=0.17, f16_exp=0) for p, _ in runs])
+        if chosen:
+            b.set_item_nodes(5000)
+        for k, (_, init) in enumerate(runs):
+            b.init_droplets(k, init["droplets"], init["rho_L"], init["rho_V"], init["W"])
+        b.step(2)
+        batches.append(b)
+    a, b = batches
+    assert a.tuning()[1] in (4096, 8192, 12288, 16384, 24576, 32768) and b.tuning()[1] == 5000
+    for k in range(count):
+        assert bool((a.read_populations(k) == b.read_populations(k)).all()), k
+    a.set_step_mode("fused")
+    b.set_step_mode("fused")
+    assert a.tuning()[1] == 8192 and b.tuning()[1] == 5000
+    a.close()
+    b.close()
