@@ -1682,8 +1682,9 @@ __global__ void __launch_bounds__(2 * SPLIT_ROLE)
 //
 // Bound by memory: every stored value is read once and written once, so
 // nothing is tiled.  A block takes 256 consecutive nodes of one z-plane, whose
-// z neighbours are then scalar, and a wall costs one select of two 32-bit
-// offsets per direction.  With a periodic wrap by division per direction and
+// z neighbours are then scalar, or (FLAT, for planes that would leave lanes
+// idle) of the lattice; a wall costs one select of two 32-bit offsets per
+// direction.  With a periodic wrap by division per direction and
 // 64-bit indices it was bound by address arithmetic: 21.7 us in FP64 at 60^3
 // and 65 us in FP32 at 110^3 (orthogonal), now 12.1 and 35 (5.4 and 5.8 TB/s
 // from the last-level cache; FP32 at 256^3 0.454 ms, 5.6 TB/s).
@@ -1696,7 +1697,7 @@ __global__ void __launch_bounds__(2 * SPLIT_ROLE)
 // ---------------------------------------------------------------------------
 constexpr int SINGLE_THREADS = 256;
 
-template <int S, int OP, bool NT>
+template <int S, int OP, bool NT, bool FLAT>
 __global__ void __launch_bounds__(SINGLE_THREADS)
     k_single(const typename Storage<S>::T *__restrict__ A, typename Storage<S>::T *__restrict__ B, GridDesc g,
              PhysD pd) {
@@ -1705,10 +1706,18 @@ __global__ void __launch_bounds__(SINGLE_THREADS)
     using T = typename ST::T;
     constexpr uint32_t EB = sizeof(T);
     const uint32_t nx = (uint32_t)g.nx, ny = (uint32_t)g.ny, plane = nx * ny;
-    const uint32_t bpp = (plane + SINGLE_THREADS - 1) / SINGLE_THREADS;  // blocks per z-plane
-    const uint32_t z = blockIdx.x / bpp;                                 // wave-uniform
-    const uint32_t i = (blockIdx.x - z * bpp) * SINGLE_THREADS + threadIdx.x;
-    if (i >= plane) return;
+    uint32_t z, i;
+    if constexpr (FLAT) {
+        const uint32_t n = blockIdx.x * SINGLE_THREADS + threadIdx.x;
+        if (n >= (uint32_t)g.N) return;
+        z = n / plane;
+        i = n - z * plane;
+    } else {
+        const uint32_t bpp = (plane + SINGLE_THREADS - 1) / SINGLE_THREADS;  // blocks per z-plane
+        z = blockIdx.x / bpp;                                                // wave-uniform
+        i = (blockIdx.x - z * bpp) * SINGLE_THREADS + threadIdx.x;
+        if (i >= plane) return;
+    }
     Phys<R> P;
     P.load(pd);
     const uint32_t y = i / nx, x = i - y * nx;
