@@ -489,9 +489,14 @@ lbm_status launch_walls(lbm_ctx *c, const void *src) {
         using T = typename Storage<S.value>::T;
         using R = typename Storage<S.value>::R;
         if (!W.value) return LBM_OK;
-        const unsigned blocks = 2u * (unsigned)((c->p.nx + WALL_X - 1) / WALL_X) * (unsigned)((c->p.ny + WALL_Y - 1) / WALL_Y);
-        hipLaunchKernelGGL(k_ghost_psi<S.value>, dim3(blocks), dim3(WALL_THREADS), 0, c->stream, (const T *)src,
-                           (R *)c->gpsi(), c->g, c->pd);
+        const int wl = wall_log2(c->p.nx, c->p.ny), wy = wall_rows(wl);
+        const unsigned blocks = 2u * (unsigned)((c->p.nx + (1 << wl) - 1) >> wl) * (unsigned)((c->p.ny + wy - 1) / wy);
+        if (wl < 5)
+            hipLaunchKernelGGL((k_ghost_psi<S.value, true>), dim3(blocks), dim3(WALL_THREADS), 0, c->stream,
+                               (const T *)src, (R *)c->gpsi(), c->g, c->pd);
+        else
+            hipLaunchKernelGGL((k_ghost_psi<S.value, false>), dim3(blocks), dim3(WALL_THREADS), 0, c->stream,
+                               (const T *)src, (R *)c->gpsi(), c->g, c->pd);
         HIP_TRY(hipGetLastError());
         return LBM_OK;
     });

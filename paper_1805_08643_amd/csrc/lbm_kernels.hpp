@@ -1927,52 +1927,68 @@ __global__ void __launch_bounds__(256)
 // Wall support, Eq. (57): ghost psi one layer beyond each wall, from the
 // densities of the first two fluid layers.
 //
-// A block takes WALL_X x WALL_Y nodes of one wall: its threads pull the second
-// layer at their own node and the first layer over the tile and its one-node
-// ring (two nodes for some threads), all loads in flight together, and the
-// densities of the first layer meet in LDS.  Bound by launch and load latency,
-// not by bytes: one launch instead of a density pass over four planes and a
-// ghost pass, which took 5.8 + 4.8 us in FP64 at 160 x 160 and 5.3 + 2.9 in
-// FP32 at 75 x 61.
+// A block takes 32 x 4 nodes of one wall, on long walls of up to 16 columns as
+// many columns as there are (a power of two) and more rows: its threads pull the
+// second layer at their own node and the first layer over the tile and its
+// one-node ring (two nodes for some threads), all loads in flight together,
+// and the densities of the first layer meet in LDS.  Bound by launch and load
+// latency, not by bytes: one launch instead of a density pass over four planes
+// and a ghost pass, which took 5.8 + 4.8 us in FP64 at 160 x 160 and 5.3 + 2.9
+// in FP32 at 75 x 61.
 // ---------------------------------------------------------------------------
-constexpr int WALL_X = 32, WALL_Y = 4, WALL_THREADS = WALL_X * WALL_Y;
-template <int S>
+constexpr int WALL_THREADS = 128;
+// Log2 of the tile's columns, and its rows.  On narrow walls 32 columns leave
+// most lanes without a node (us a step with them and without: FP64 1 x 100000 x
+// 2 180 and 39, FP32 4 x 30000 x 2 42 and 24), and strips of 2^26 rows would
+// need more than the 2^32 threads that a launch can have; so every lattice
+// whose five planes fit 4 GiB stays below.  Up to 1024 rows a 32 x 4 tile's
+// blocks all fit the chip at once, and the fixed tile's shorter code is faster
+// (11.7 against 12.1 us in FP32 at 5 x 300 x 40).
+__host__ __device__ inline int wall_log2(int nx, int ny) {
+    return nx > 16 || ny <= 1024 ? 5 : nx > 8 ? 4 : nx > 4 ? 3 : nx > 2 ? 2 : nx - 1;
+}
+__host__ __device__ inline int wall_rows(int wl) {  // at most two first-layer nodes per thread
+    const int lanes = WALL_THREADS >> wl, ring = 2 * WALL_THREADS / ((1 << wl) + 2) - 2;
+    return lanes < ring ? lanes : ring;
+}
+// NARROW: any tile; otherwise the 32 x 4 one, known when compiled.
+template <int S, bool NARROW>
 __global__ void __launch_bounds__(WALL_THREADS)
     k_ghost_psi(const typename Storage<S>::T *__restrict__ A, typename Storage<S>::R *__restrict__ gpsi, GridDesc g,
                 PhysD pd) {
     using R = typename Storage<S>::R;
-    constexpr int SX = WALL_X + 2, EXT = SX * (WALL_Y + 2);
-    static_assert(EXT <= 2 * WALL_THREADS, "two first-layer nodes per thread");
-    __shared__ R l1[EXT];
+    __shared__ R l1[2 * WALL_THREADS];
     Phys<R> P;
     P.load(pd);
     const int nx = g.nx, ny = g.ny, nz = g.nz;
-    const int bx = (nx + WALL_X - 1) / WALL_X, by = (ny + WALL_Y - 1) / WALL_Y;
+    const int wl = NARROW ? wall_log2(nx, ny) : 5;
+    const int WX = 1 << wl, WY = wall_rows(wl), SX = WX + 2, ext = SX * (WY + 2);
+    const int bx = (nx + WX - 1) >> wl, by = (ny + WY - 1) / WY;
     const int side = blockIdx.x >= (unsigned)(bx * by);
     const int b = blockIdx.x - side * bx * by;
-    const int x0 = b % bx * WALL_X, y0 = b / bx * WALL_Y;
+    const int x0 = b % bx * WX, y0 = b / bx * WY;
     const int z1 = side ? nz - 1 : 0, z2 = side ? nz - 2 : 1;
     const int tid = threadIdx.x;
     // Node k of the tile and its ring, clamped to the ring of the lattice and wrapped.
     auto node = [&](int k, int &x, int &y) {
-        const int ky = k / SX;
+        const int ky = NARROW ? (int)(((float)k + 0.5f) * __builtin_amdgcn_rcpf((float)SX)) : k / SX;
         x = min(x0 + k - ky * SX - 1, nx);
         y = min(y0 + ky - 1, ny);
         x = x < 0 ? nx - 1 : (x == nx ? 0 : x);
         y = y < 0 ? ny - 1 : (y == ny ? 0 : y);
     };
-    const int x = x0 + tid % WALL_X, y = y0 + tid / WALL_X;
+    const int x = x0 + (tid & (WX - 1)), y = y0 + (tid >> wl);
     int xa, ya, xb, yb;
     node(tid, xa, ya);
-    node(min(tid + WALL_THREADS, EXT - 1), xb, yb);
+    node(min(tid + WALL_THREADS, ext - 1), xb, yb);
     const R rho2 = density_at<S, true>(A, g, min(x, nx - 1), min(y, ny - 1), z2, P);
     const R rhoa = density_at<S, true>(A, g, xa, ya, z1, P);
     const R rhob = density_at<S, true>(A, g, xb, yb, z1, P);
     l1[tid] = rhoa;
-    if (tid + WALL_THREADS < EXT) l1[tid + WALL_THREADS] = rhob;
+    if (tid + WALL_THREADS < ext) l1[tid + WALL_THREADS] = rhob;
     __syncthreads();
-    if (x >= nx || y >= ny) return;
-    const int c = (tid / WALL_X + 1) * SX + tid % WALL_X + 1;
+    if (x >= nx || y >= ny || (tid >> wl) >= WY) return;
+    const int c = ((tid >> wl) + 1) * SX + (tid & (WX - 1)) + 1;
     const R dx = l1[c + 1] - l1[c - 1], dy = l1[c + SX] - l1[c - SX];
     const R phi = r_sqrt(dx * dx + dy * dy);
     R rg = rho2 + phi * P.tan_wall;
