@@ -38,6 +38,15 @@ struct GridDesc {
 // took more instructions than pulling a node: in a tile's setup, which short z
 // runs do not amortise, and 54 times per node in the readback kernels.
 __device__ inline int wrapi(int v, int n) { return v < 0 ? n - 1 : (v >= n ? 0 : v); }
+// The same for the plane of a march, which every lane of a wave shares.  Left
+// to itself the compiler may keep it in a vector register (it did where the
+// wrap became two selects), and then puts every load whose scalar offset
+// follows from it into a loop over the lanes' values: 588 against 394 us in
+// F16S pairs and 457 against 380 in quads at 256^3.  Added up, it takes fewer
+// registers than selected: the orthogonal quads spill 8 against 10.
+__device__ inline int wrap_plane(int z, int n) {
+    return __builtin_amdgcn_readfirstlane(z + (z < 0 ? n : 0) - (z >= n ? n : 0));
+}
 
 // Blocks are dealt to the 8 XCDs round-robin; give each XCD a contiguous run
 // of tiles so that tiles sharing halo rows share an L2.
@@ -787,7 +796,7 @@ __device__ inline void tile_march2(const typename Storage<S>::T *__restrict__ A,
 
     auto issue = [&](int zp, R *fa, R *fb) {
         if (WALL && (zp < 0 || zp >= nz)) return;
-        const int zw = WALL ? zp : wrapi(zp, nz);
+        const int zw = WALL ? zp : wrap_plane(zp, nz);
         if (need_in) pull2<S, WALL>(bA, nz, PB, zw, oin, wl, wr, P, fa, fb);
         if (halo) pull<S, WALL>(bA, nz, PB, zw, oh, P, fh);
     };
@@ -1167,7 +1176,7 @@ __device__ inline void tile_march4(const uint16_t *__restrict__ A, uint16_t *__r
 
     Wide8 cq, nq;  // planes z and z + 1, storage format
     R rc[4] = {1, 1, 1, 1}, rn[4] = {1, 1, 1, 1};
-    auto zwrap = [&](int zp) { return WALL ? zp : wrapi(zp, nz); };
+    auto zwrap = [&](int zp) { return WALL ? zp : wrap_plane(zp, nz); };
     auto slot_of = [&](int z) { return ps + ((z - zb + 1) & 3) * SP; };
     // Pull plane zp into q and put its psi in LDS; densities into rho.
     auto pull_plane = [&](int zp, Wide8 &q, R *rho) {
