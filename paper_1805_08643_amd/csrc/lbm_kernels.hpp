@@ -309,10 +309,14 @@ __device__ inline void lds_barrier() {
 // AHEAD: the loads of plane z + 2 are issued before plane z is collided and
 // waited for after it is stored.  That takes a third set of registers: 168
 // VGPRs, just three waves per SIMD, for the periodic non-orthogonal FP32
-// kernel, where it gains 3-7% (132 against 143 us at 150^3, 31.0 against 32.2
-// at 101 x 97 x 89); with walls, the orthogonal operator or F16S it needs more,
-// loses the third wave and measured slower (19.5 against 18.4 us on a walled
-// 75 x 61 x 43), and in FP64 it spills.
+// kernel, where it gains 3-20% (132 against 143 us at 150^3, 31.0 against 32.2
+// at 101 x 97 x 89, 581 against 623 at 256^3 with 128 x 4 tiles); with walls,
+// the orthogonal operator or F16S it needs more, loses the third wave and
+// measured slower (19.5 against 18.4 us on a walled 75 x 61 x 43), and in FP64
+// it spills.
+// PACE: instead, a plane's loads wait until the stores of the plane before
+// have been taken.  For blocks of few waves of which a CU holds several; the
+// rule and what it measured are with the launch (paced_march).
 //
 // Bound by the address unit at about 70% of the time the compute units are
 // busy (8.4 cycles per wave access: rows that do not start on 64 bytes take
@@ -321,7 +325,7 @@ __device__ inline void lds_barrier() {
 // measured (best tile of a sweep each) 5.8 against 6.4 us at 32^3 and 132
 // against 146 at 150^3 in FP32, 7.8 against 8.5 at 32^3 and 1118 against 1154 at
 // 256^3 in FP64.
-template <int S, int OP, bool WALL>
+template <int S, int OP, bool WALL, bool PACE = false>
 __device__ inline void tile_march(const typename Storage<S>::T *__restrict__ A,
                                   typename Storage<S>::T *__restrict__ B,
                                   const typename Storage<S>::R *__restrict__ gpsi, const GridDesc &g,
@@ -329,7 +333,7 @@ __device__ inline void tile_march(const typename Storage<S>::T *__restrict__ A,
                                   typename Storage<S>::R *ps) {
     using ST = Storage<S>;
     using R = typename ST::R;
-    constexpr bool AHEAD = S == ST_F32 && OP == OP_NONORTH && !WALL;
+    constexpr bool AHEAD = S == ST_F32 && OP == OP_NONORTH && !WALL && !PACE;
     const int TX = g.tx, TY = g.ty;
     const int SX = TX + 2, SP = (TY + 2) * SX;
     int t = tile;
@@ -470,6 +474,7 @@ __device__ inline void tile_march(const typename Storage<S>::T *__restrict__ A,
         R f0[Q], f1[Q], fh[Q];
         R r0, r1;
         auto fetch = [&](int z, R *f) {
+            if constexpr (PACE) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
             load(z, oin, f);
             if (wave_halo) {
                 load(z, oh, fh);
@@ -513,7 +518,7 @@ constexpr int STEP_MAX_THREADS = LBM_STEP_MAX_THREADS;
 #define LBM_STEP_ATTR __launch_bounds__(STEP_MAX_THREADS)
 #endif
 
-template <int S, int OP, bool WALL>
+template <int S, int OP, bool WALL, bool PACE = false>
 __global__ void LBM_STEP_ATTR
     k_step(const typename Storage<S>::T *__restrict__ A, typename Storage<S>::T *__restrict__ B,
            const typename Storage<S>::R *__restrict__ gpsi, GridDesc g, PhysD pd) {
@@ -524,7 +529,7 @@ __global__ void LBM_STEP_ATTR
     if (tile >= g.ntiles) return;
     Phys<R> P;
     P.load(pd);
-    tile_march<S, OP, WALL>(A, B, gpsi, g, P, tile, ps);
+    tile_march<S, OP, WALL, PACE>(A, B, gpsi, g, P, tile, ps);
 }
 
 // ---------------------------------------------------------------------------
