@@ -1358,16 +1358,22 @@ size_t batch_total(const lbm_params *runs, int32_t n, std::vector<size_t> *offs,
 // strides over the items, so a step ends with the block that has most to march:
 // the item size is the one whose most loaded block has least, an item costing
 // its columns times its planes and two more.  Many runs take long items (fewer
-// planes read twice), few runs short ones (no block idle).  Measured, us a step
-// with 8192 nodes for all and so: 64 runs of 32^3 to 96^3 525 -> 470 with F16S,
-// 606 -> 521 with F16N; 20 runs 145 -> 139 and 165 -> 153; 6 runs, and FP32,
-// keep 8192.  The other steps' items are within 2% of their best at 8192.
+// planes read twice), few runs short ones (no block idle).  FP32 batches of
+// many runs are bound by memory, which this does not count: there a size that
+// promised up to 6% took up to 5% more time (256 runs of 32^3 to 96^3 2890 us a
+// step with 12288 nodes, 2740 with 8192), so FP32 leaves 8192 for 8% or more.
+// Measured over 204 batches of 2 to 256 runs of 32^3 to 128^3, the pick takes
+// 1.010 times the best size's time with FP32 and 1.002 with F16S and F16N in
+// the geometric mean, and at most 1.013 times that of 8192: us a step with 8192
+// for all and so, 64 runs of 32^3 to 96^3 604 -> 562 with F16S, 686 -> 632 with
+// F16N; 6 runs 80 -> 54, 103 -> 66 and 92 -> 62 with FP32.  The other steps'
+// items are within 2% of their best at 8192.
 int default_items(const lbm_batch *b) {
     constexpr int ITEMS = 8192;
     if (b->mode != LBM_STEP_SPLIT) return ITEMS;
     int best = ITEMS;
-    long long least = std::numeric_limits<long long>::max();
-    for (int size : {8192, 4096, 12288, 16384, 24576, 32768}) {
+    long long least = std::numeric_limits<long long>::max(), enough = least;
+    for (int size : {ITEMS, 4096, 12288, 16384, 24576, 32768}) {
         long long n = 0;
         GridDesc g{};
         for (const lbm_ctx *c : b->runs) {
@@ -1384,10 +1390,11 @@ int default_items(const lbm_batch *b) {
                         (long long)g.tx * g.ty * (std::min(g.cz, g.nz - k * g.cz) + 2);
         }
         const long long most = *std::max_element(load, load + 256);
-        if (most < least) {
+        if (most < least && most <= enough) {
             least = most;
             best = size;
         }
+        if (size == ITEMS && b->storage == ST_F32) enough = most - most * 8 / 100;
     }
     return best;
 }
