@@ -315,32 +315,59 @@ void fill_grid(GridDesc &g, const lbm_params &p, const lbm_tile &t) {
 // the geometric mean of each step; the tiles used before it, made for 256^3
 // and with runs of at least 8 planes, took 1.45 (FP32 split) to 3.3 times
 // (F16S pairs).
-double tile_cost(int nx, int ny, int nz, int npt, int storage, bool split, const lbm_tile &t) {
-    constexpr double START = 1.0, PLANE = 1.8, WAVE = 0.13, HALO = 0.5;  // us a block, a plane, a wave; a halo wave's part
-    constexpr double HBM = 3.4e6, CACHE = 5.8e6;                         // bytes per us
-    constexpr double TAIL = 0.8;                                         // cost of the empty part of a last round
-    constexpr double LINE = 0.3, WHOLE = 0.5;                            // of a line a piece read twice; of whole lines
-    constexpr double ROWS = 0.2, PLANES = 0.3;                           // of a row a column, of a plane a run read twice
-    const double per_simd = storage == ST_F64 || npt > 1 ? 2 : 3;        // waves a SIMD's registers hold
-    const double ntiles = std::ceil((double)nx / t.tx) * std::ceil((double)ny / t.ty) * std::ceil((double)nz / t.cz);
-    const double iw = (t.tx / npt * t.ty + 63) / 64, hw = (2 * (t.tx + 2) + 2 * t.ty + 63) / 64;
-    // Blocks of a CU; a block of five waves takes two of a SIMD's places.
-    const double resident = split ? 1.0 : std::max(1.0, std::floor(per_simd / std::ceil(std::max(iw, hw) / 4)));
-    const double per_xcd = std::ceil(ntiles / 8), x = per_xcd / (32 * resident);
-    const double rounds = x <= 1 ? 1.0 : x + TAIL * (std::ceil(x) - x);
-    const double k = std::min(resident, std::ceil(per_xcd / 32));
-    const double march = rounds * (START + (t.cz + 2) * (PLANE + WAVE * k * (iw + HALO * hw)));
-    const int size = storage == ST_F64 ? 8 : storage == ST_F32 ? 4 : 2;
-    const double pops = (double)nx * ny * nz * size * (storage == ST_F16N ? 20 : 19);
-    // A wave takes one row or parts of several: a piece starts with every row and with every wave.
-    const int per_row = t.tx / npt, n = per_row * t.ty;
-    const double pieces = t.ty + (n + 63) / 64 - (n + std::lcm(per_row, 64) - 1) / std::lcm(per_row, 64);
-    const double line = (t.tx * size % 128 ? LINE : LINE * WHOLE) * 128 * pieces / ((double)t.tx * t.ty * size);
-    const double bytes = pops * (1 + (1 + line) * (1 + PLANES / t.cz) * (1 + ROWS / t.ty));
-    const double busy = per_xcd / (32 * k * std::ceil(per_xcd / (32 * k)));
-    const double move = bytes / ((2 * pops > (double)kLlcBytes ? HBM : CACHE) * std::sqrt(std::sqrt(busy)));
-    return march * march * march + move * move * move;
-}
+//
+// TileCost holds what a lattice's tiles share, columns() adds what the z runs
+// of a tile's columns share, and run() is the cost with runs of cz planes.
+struct TileCost {
+    static constexpr double START = 1.0, PLANE = 1.8, WAVE = 0.13, HALO = 0.5;  // us a block, a plane, a wave; a halo wave's part
+    static constexpr double HBM = 3.4e6, CACHE = 5.8e6;                         // bytes per us
+    static constexpr double TAIL = 0.8;                                         // cost of the empty part of a last round
+    static constexpr double LINE = 0.3, WHOLE = 0.5;                            // of a line a piece read twice; of whole lines
+    static constexpr double ROWS = 0.2, PLANES = 0.3;                           // of a row a column, of a plane a run read twice
+    int nx, ny, nz, npt, size, per_simd;
+    bool split;
+    double pops, rate;  // bytes of a population array; bytes per us
+    long long cols = 0;
+    double waves = 0, again = 0;  // of a block a plane; populations read, for each written, by runs of the whole height
+    int resident = 1;             // blocks of a CU
+
+    TileCost(int nx_, int ny_, int nz_, int npt_, int storage, bool split_)
+        : nx(nx_), ny(ny_), nz(nz_), npt(npt_), size(storage == ST_F64 ? 8 : storage == ST_F32 ? 4 : 2),
+          per_simd(storage == ST_F64 || npt_ > 1 ? 2 : 3),  // waves a SIMD's registers hold
+          split(split_), pops((double)nx_ * ny_ * nz_ * size * (storage == ST_F16N ? 20 : 19)) {
+        rate = 2 * pops > (double)kLlcBytes ? HBM : CACHE;
+    }
+    void columns(int tx, int ty) {
+        cols = (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
+        const int iw = (tx / npt * ty + 63) / 64, hw = (2 * (tx + 2) + 2 * ty + 63) / 64;
+        waves = iw + HALO * hw;
+        // A block of five waves takes two of a SIMD's places.
+        resident = split ? 1 : std::max(1, per_simd / ((std::max(iw, hw) + 3) / 4));
+        // A wave takes one row or parts of several: a piece starts with every row and with every wave.
+        const int per_row = tx / npt, n = per_row * ty, period = std::lcm(per_row, 64);
+        const int pieces = ty + (n + 63) / 64 - (n + period - 1) / period;
+        const double line = (tx * size % 128 ? LINE : LINE * WHOLE) * 128 * pieces / ((double)tx * ty * size);
+        again = (1 + line) * (1 + ROWS / ty);
+    }
+    // No run length has a cost below this.
+    double bound() const {
+        const double move = pops * (1 + again * (1 + PLANES / nz)) / rate;
+        return move * move * move;
+    }
+    // The cost, or something that is not below least.
+    double run(int cz, double least) const {
+        const long long ntiles = cols * ((nz + cz - 1) / cz), per_xcd = (ntiles + 7) / 8, chip = 32ll * resident;
+        const double x = (double)per_xcd / chip, whole = (double)((per_xcd + chip - 1) / chip);
+        const double rounds = x <= 1 ? 1.0 : x + TAIL * (whole - x);
+        const long long k = std::min<long long>(resident, (per_xcd + 31) / 32);
+        const double march = rounds * (START + (cz + 2.0) * (PLANE + WAVE * k * waves));
+        const double march3 = march * march * march;
+        if (march3 >= least) return march3;
+        const double busy = (double)per_xcd / (32 * k * ((per_xcd + 32 * k - 1) / (32 * k)));
+        const double move = pops * (1 + again * (1 + PLANES / cz)) / (rate * std::sqrt(std::sqrt(busy)));
+        return march3 + move * move * move;
+    }
+};
 
 // Default tile of a step that takes npt nodes per thread: the cheapest of the
 // tiles that cut x, y and z into equal parts (rows of 24 to 256 nodes, at least
@@ -355,6 +382,7 @@ double tile_cost(int nx, int ny, int nz, int npt, int storage, bool split, const
 lbm_tile search_tile(int nx, int ny, int nz, int npt, int storage, bool split) {
     lbm_tile best{std::min(nx, 24) / npt * npt, 1, nz, 0};
     double least = std::numeric_limits<double>::infinity();
+    TileCost cost(nx, ny, nz, npt, storage, split);
     auto cuts = [](int n, int part) { return (int)(((long long)n + part - 1) / part); };
     // The largest part of an equal cut of n that is at most this one.
     auto equal = [&](int n, int part) { return part > 0 ? cuts(n, cuts(n, part)) : 0; };
@@ -368,13 +396,14 @@ lbm_tile search_tile(int nx, int ny, int nz, int npt, int storage, bool split) {
             if (split ? !split_tile_fits(t, npt, storage) : !step_tile_fits(t, storage, npt)) continue;
             if (!tallest && t.tx / npt * t.ty < 60) break;
             tallest = false;
-            const double cols = (double)cuts(nx, t.tx) * cuts(ny, h);
+            cost.columns(t.tx, h);
+            if (cost.bound() >= least) continue;
             for (int d = nz; d >= 1; d = equal(nz, d - 1)) {
-                t.cz = d;
-                if (d < nz && cols * cuts(nz, d) > 6000) break;
-                const double cost = tile_cost(nx, ny, nz, npt, storage, split, t);
-                if (cost < least) {
-                    least = cost;
+                if (d < nz && cost.cols * cuts(nz, d) > 6000) break;
+                const double c = cost.run(d, least);
+                if (c < least) {
+                    least = c;
+                    t.cz = d;
                     best = t;
                 }
             }
@@ -383,23 +412,28 @@ lbm_tile search_tile(int nx, int ny, int nz, int npt, int storage, bool split) {
     return best;
 }
 
-// search_tile takes up to 0.4 ms of host time, which a step without a context
-// would pay on every call and a batch for every run, so each thread keeps its
-// last answers; the tile follows from the arguments alone.
+// search_tile takes 2 us of host time for 32^3, 15 to 40 for 256^3, which a step
+// without a context would pay on every call, so each thread keeps answers: the
+// last four of each of 64 sets (5 us a call went into the search where a caller
+// stepped nine or more small lattices in turn and eight were kept in all).  The
+// tile follows from the arguments alone.
 lbm_tile pick_tile(const lbm_params &p, int mode) {
+    constexpr int SETS = 64, WAYS = 4;
     struct Answer {
-        int nx, ny, nz, npt, storage, split;
+        int nx, ny, nz, key;
         lbm_tile tile;
     };
-    static thread_local Answer kept[8]{};
-    static thread_local int oldest = 0;
-    const int npt = npt_of(mode, p.storage), split = mode == LBM_STEP_SPLIT;
-    for (const Answer &k : kept)
-        if (k.nx == p.nx && k.ny == p.ny && k.nz == p.nz && k.npt == npt && k.storage == p.storage && k.split == split)
-            return k.tile;
+    static thread_local Answer kept[SETS][WAYS]{};
+    const int npt = npt_of(mode, p.storage);
+    const bool split = mode == LBM_STEP_SPLIT;
+    const int key = npt * 8 + p.storage * 2 + split;  // never 0: no answer yet
+    const uint64_t hash = (((uint64_t)p.nx * 0x9E3779B97F4A7C15u + p.ny) * 0x9E3779B97F4A7C15u + p.nz) * 0x9E3779B97F4A7C15u + key;
+    Answer *set = kept[(hash * 0x9E3779B97F4A7C15u) >> 58];
+    for (int w = 0; w < WAYS; ++w)
+        if (set[w].key == key && set[w].nx == p.nx && set[w].ny == p.ny && set[w].nz == p.nz) return set[w].tile;
     const lbm_tile t = search_tile(p.nx, p.ny, p.nz, npt, p.storage, split);
-    kept[oldest] = {p.nx, p.ny, p.nz, npt, p.storage, split, t};
-    oldest = (oldest + 1) % 8;
+    std::copy_backward(set, set + WAYS - 1, set + WAYS);  // the newest first
+    set[0] = {p.nx, p.ny, p.nz, key, t};
     return t;
 }
 
@@ -724,8 +758,35 @@ void default_mode(lbm_ctx *c) {
     } else {
         c->mode = LBM_STEP_FUSED;
     }
-    c->tile = pick_tile(p, c->mode);
-    fill_grid(c->g, p, c->tile);
+}
+
+void default_tile(lbm_ctx *c) {
+    c->tile = pick_tile(c->p, c->mode);
+    fill_grid(c->g, c->p, c->tile);
+}
+
+// A context over dev_ws in its default step mode, without a tile.
+lbm_status new_ctx(const lbm_params *p, void *dev_ws, size_t ws_bytes, void *hip_stream, lbm_ctx **out) {
+    lbm_status s = validate(p);
+    if (s) return s;
+    if (!out) return fail(LBM_ERR_INVALID_ARG, "out is NULL");
+    *out = nullptr;
+    if (!dev_ws) return fail(LBM_ERR_INVALID_ARG, "workspace is NULL");
+    if (reinterpret_cast<uintptr_t>(dev_ws) % kAlign)
+        return fail(LBM_ERR_INVALID_ARG, "workspace must be %zu-byte aligned", kAlign);
+    Layout L = layout_of(*p);
+    if (ws_bytes < L.total)
+        return fail(LBM_ERR_BUFFER_TOO_SMALL, "workspace %zu bytes < required %zu", ws_bytes, L.total);
+    lbm_ctx *c = new (std::nothrow) lbm_ctx();
+    if (!c) return fail(LBM_ERR_INVALID_ARG, "out of host memory");
+    c->p = *p;
+    c->pd = make_phys(*p);
+    c->L = L;
+    c->ws = static_cast<unsigned char *>(dev_ws);
+    c->stream = static_cast<hipStream_t>(hip_stream);
+    default_mode(c);
+    *out = c;
+    return LBM_OK;
 }
 
 // Device address of the allocation-free step's scratch array on the current
@@ -842,26 +903,9 @@ lbm_status lbm_workspace_bytes(const lbm_params *p, size_t *bytes) {
 }
 
 lbm_status lbm_create(const lbm_params *p, void *dev_ws, size_t ws_bytes, void *hip_stream, lbm_ctx **out) {
-    lbm_status s = validate(p);
-    if (s) return s;
-    if (!out) return fail(LBM_ERR_INVALID_ARG, "out is NULL");
-    *out = nullptr;
-    if (!dev_ws) return fail(LBM_ERR_INVALID_ARG, "workspace is NULL");
-    if (reinterpret_cast<uintptr_t>(dev_ws) % kAlign)
-        return fail(LBM_ERR_INVALID_ARG, "workspace must be %zu-byte aligned", kAlign);
-    Layout L = layout_of(*p);
-    if (ws_bytes < L.total)
-        return fail(LBM_ERR_BUFFER_TOO_SMALL, "workspace %zu bytes < required %zu", ws_bytes, L.total);
-    lbm_ctx *c = new (std::nothrow) lbm_ctx();
-    if (!c) return fail(LBM_ERR_INVALID_ARG, "out of host memory");
-    c->p = *p;
-    c->pd = make_phys(*p);
-    c->L = L;
-    c->ws = static_cast<unsigned char *>(dev_ws);
-    c->stream = static_cast<hipStream_t>(hip_stream);
-    default_mode(c);
-    *out = c;
-    return LBM_OK;
+    lbm_status s = new_ctx(p, dev_ws, ws_bytes, hip_stream, out);
+    if (s == LBM_OK) default_tile(*out);
+    return s;
 }
 
 lbm_status lbm_destroy(lbm_ctx *c) {
@@ -974,6 +1018,7 @@ lbm_status lbm_step_noalloc(const lbm_params *p, const void *dev_src, void *dev_
     c.stream = static_cast<hipStream_t>(hip_stream);
     c.wall_scratch = scr;
     default_mode(&c);
+    default_tile(&c);
     if ((s = step_walls(&c, dev_src))) return s;
     return launch_step(&c, c.g, dev_src, dev_dst, npt_of(c.mode, p->storage));
 }
@@ -1373,22 +1418,37 @@ int default_items(const lbm_batch *b) {
     if (b->mode != LBM_STEP_SPLIT) return ITEMS;
     int best = ITEMS;
     long long least = std::numeric_limits<long long>::max(), enough = least;
+    struct Items {  // of a run: layers of tiles in z, tiles of a layer, load of one and of one of the last layer
+        int layers, tiles;
+        long long load, last;
+    };
+    std::vector<Items> runs(b->runs.size());
     for (int size : {ITEMS, 4096, 12288, 16384, 24576, 32768}) {
-        long long n = 0;
-        GridDesc g{};
-        for (const lbm_ctx *c : b->runs) {
-            fill_grid(g, c->p, batch_tile(c->p, size, b->mode));
-            n += g.ntiles;
+        long long n = 0, total = 0;
+        for (size_t r = 0; r < runs.size(); ++r) {
+            const lbm_params &p = b->runs[r]->p;
+            const lbm_tile t = batch_tile(p, size, b->mode);
+            const int layers = (p.nz + t.cz - 1) / t.cz, tiles = ((p.nx + t.tx - 1) / t.tx) * ((p.ny + t.ty - 1) / t.ty);
+            const long long cols = (long long)t.tx * t.ty;
+            runs[r] = {layers, tiles, cols * (t.cz + 2), cols * (p.nz - (layers - 1) * t.cz + 2)};
+            n += (long long)layers * tiles;
+            total += tiles * ((layers - 1) * runs[r].load + runs[r].last);
         }
-        const long long blocks = std::min(n, 256ll), per_xcd = (n + 7) / 8;
-        long long load[256] = {}, item = 0;
-        for (const lbm_ctx *c : b->runs) {
-            fill_grid(g, c->p, batch_tile(c->p, size, b->mode));
-            for (int k = 0; k < g.nzc; ++k)
-                for (int t = 0; t < g.ntx * g.nty; ++t, ++item)  // xcd_tile's order, backwards
-                    load[(item % per_xcd * 8 + item / per_xcd) % blocks] +=
-                        (long long)g.tx * g.ty * (std::min(g.cz, g.nz - k * g.cz) + 2);
-        }
+        const long long per_xcd = (n + 7) / 8;
+        const int blocks = (int)std::min(n, 256ll);
+        if (total / blocks >= least) continue;  // the most loaded block has no less than the mean
+        long long load[256] = {}, left = per_xcd;
+        int xcd = 0, block = 0;
+        for (const Items &it : runs)
+            for (int k = 0; k < it.layers; ++k)
+                for (int t = 0; t < it.tiles; ++t) {  // xcd_tile's order, backwards
+                    load[block] += k + 1 < it.layers ? it.load : it.last;
+                    for (block += 8; block >= blocks;) block -= blocks;
+                    if (--left == 0) {
+                        left = per_xcd;
+                        block = ++xcd % blocks;
+                    }
+                }
         const long long most = *std::max_element(load, load + 256);
         if (most < least && most <= enough) {
             least = most;
@@ -1559,7 +1619,7 @@ lbm_status lbm_batch_create(const lbm_params *runs, int32_t n, void *dev_ws, siz
     b->mode = all_split ? LBM_STEP_SPLIT : batch_pairs_apply(runs, n) ? LBM_STEP_PAIRS : LBM_STEP_FUSED;
     for (int k = 0; k < n; ++k) {
         lbm_ctx *c = nullptr;
-        s = lbm_create(&runs[k], b->ws + b->run_off[k], layout_of(runs[k]).total, hip_stream, &c);
+        s = new_ctx(&runs[k], b->ws + b->run_off[k], layout_of(runs[k]).total, hip_stream, &c);  // tiles: batch_build
         if (s) {
             lbm_batch_destroy(b);
             return s;
