@@ -305,80 +305,96 @@ void fill_grid(GridDesc &g, const lbm_params &p, const lbm_tile &t) {
 // out, with more read again the shorter a tile's columns, its z runs and the
 // pieces of rows that its waves take are (pieces that start and end inside
 // 128-byte lines most), at the rate of the last-level cache or of HBM, and
-// somewhat slower while CUs are idle.  The sum
-// of third powers is a smooth maximum of the two.
+// somewhat slower while CUs are idle.  The sum of third powers is a smooth
+// maximum of the two.
 //
-// The constants were fitted to measured times: 119 lattices from 24 to 384
-// nodes a side with some 200 tiles each, all storages, with and without walls,
-// one, two and four nodes per thread and the split step.  One set serves all
-// of them: its pick takes 1.00 to 1.03 times the best measured tile's time in
-// the geometric mean of each step; the tiles used before it, made for 256^3
-// and with runs of at least 8 planes, took 1.45 (FP32 split) to 3.3 times
-// (F16S pairs).
+// The constants were fitted to measured times.  MARCH, for all steps but FP32's
+// split one, to 119 lattices from 24 to 384 nodes a side with some 200 tiles
+// each, all storages, with and without walls, one, two and four nodes per
+// thread and the split step; on 433 more its picks take 1.01 (16-bit steps),
+// 1.02 (FP64) and 1.06 times (FP32, one node) the best measured tile's time in
+// the geometric mean.  With them FP32's split step took narrow tiles where rows
+// do not start on 128 bytes and tiles share a line of each row (711 us a step
+// at 220^3, 394 now); SPLIT32 counts that line, loaded and stored, and was
+// fitted to 259 lattices with some 140 tiles each: 1.014 times the best tile's
+// time, at most 1.15.
 //
 // TileCost holds what a lattice's tiles share, columns() adds what the z runs
 // of a tile's columns share, and run() is the cost with runs of cz planes.
 struct TileCost {
-    static constexpr double START = 1.0, PLANE = 1.8, WAVE = 0.13, HALO = 0.5;  // us a block, a plane, a wave; a halo wave's part
-    static constexpr double HBM = 3.4e6, CACHE = 5.8e6;                         // bytes per us
-    static constexpr double TAIL = 0.8;                                         // cost of the empty part of a last round
-    static constexpr double LINE = 0.3, WHOLE = 0.5;                            // of a line a piece read twice; of whole lines
-    static constexpr double ROWS = 0.2, PLANES = 0.3;                           // of a row a column, of a plane a run read twice
+    struct Constants {
+        double start, plane, wave, halo;  // us a block, a plane, a wave; a halo wave's part
+        double hbm, cache;                // bytes per us
+        double tail;                      // cost of the empty part of a last round
+        double line, whole;               // of a line a piece read twice; of whole lines
+        double edge;                      // of a line a row of a tile, beyond the last-level cache
+        double rows, planes;              // of a row a column, of a plane a run read twice
+    };
+    static constexpr Constants MARCH = {1.0, 1.8, 0.13, 0.5, 3.4e6, 5.8e6, 0.8, 0.3, 0.5, 0.0, 0.2, 0.3};
+    static constexpr Constants SPLIT32 = {7.0, 1.8, 0.09, 0.4, 3.15e6, 3.4e6, 1.0, 0.47, 0.7, 0.17, 0.19, 0.6};
+    Constants c;
     int nx, ny, nz, npt, size, per_simd;
     bool split;
     double pops, rate;  // bytes of a population array; bytes per us
     long long cols = 0;
-    double waves = 0, again = 0;  // of a block a plane; populations read, for each written, by runs of the whole height
-    int resident = 1;             // blocks of a CU
+    double waves = 0;  // of a block a plane
+    double once = 0, again = 0;  // populations written and, but for the ends of z runs, read, in sizes of the array
+    int resident = 1;  // blocks of a CU
 
     TileCost(int nx_, int ny_, int nz_, int npt_, int storage, bool split_)
-        : nx(nx_), ny(ny_), nz(nz_), npt(npt_), size(storage == ST_F64 ? 8 : storage == ST_F32 ? 4 : 2),
+        : c(split_ && storage == ST_F32 ? SPLIT32 : MARCH), nx(nx_), ny(ny_), nz(nz_), npt(npt_),
+          size(storage == ST_F64 ? 8 : storage == ST_F32 ? 4 : 2),
           per_simd(storage == ST_F64 || npt_ > 1 ? 2 : 3),  // waves a SIMD's registers hold
           split(split_), pops((double)nx_ * ny_ * nz_ * size * (storage == ST_F16N ? 20 : 19)) {
-        rate = 2 * pops > (double)kLlcBytes ? HBM : CACHE;
+        rate = 2 * pops > (double)kLlcBytes ? c.hbm : c.cache;
     }
     void columns(int tx, int ty) {
         cols = (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
         const int iw = (tx / npt * ty + 63) / 64, hw = (2 * (tx + 2) + 2 * ty + 63) / 64;
-        waves = iw + HALO * hw;
+        waves = iw + c.halo * hw;
         // A block of five waves takes two of a SIMD's places.
         resident = split ? 1 : std::max(1, per_simd / ((std::max(iw, hw) + 3) / 4));
         // A wave takes one row or parts of several: a piece starts with every row and with every wave.
         const int per_row = tx / npt, n = per_row * ty, period = std::lcm(per_row, 64);
         const int pieces = ty + (n + 63) / 64 - (n + period - 1) / period;
-        const double line = (tx * size % 128 ? LINE : LINE * WHOLE) * 128 * pieces / ((double)tx * ty * size);
-        again = (1 + line) * (1 + ROWS / ty);
+        const bool row_lines = (long long)nx * size % 128 == 0 || !split;
+        const double part = row_lines && tx * size % 128 == 0 ? c.line * c.whole : c.line;
+        const double line = part * 128 * pieces / ((double)tx * ty * size);
+        once = row_lines || rate == c.cache ? 1 : 1 + 2 * c.edge * 128 / (tx * size);
+        again = (1 + line) * (1 + c.rows / ty);
     }
     // No run length has a cost below this.
     double bound() const {
-        const double move = pops * (1 + again * (1 + PLANES / nz)) / rate;
+        const double move = pops * (once + again * (1 + c.planes / nz)) / rate;
         return move * move * move;
     }
     // The cost, or something that is not below least.
     double run(int cz, double least) const {
         const long long ntiles = cols * ((nz + cz - 1) / cz), per_xcd = (ntiles + 7) / 8, chip = 32ll * resident;
         const double x = (double)per_xcd / chip, whole = (double)((per_xcd + chip - 1) / chip);
-        const double rounds = x <= 1 ? 1.0 : x + TAIL * (whole - x);
+        const double rounds = x <= 1 ? 1.0 : x + c.tail * (whole - x);
         const long long k = std::min<long long>(resident, (per_xcd + 31) / 32);
-        const double march = rounds * (START + (cz + 2.0) * (PLANE + WAVE * k * waves));
+        const double march = rounds * (c.start + (cz + 2.0) * (c.plane + c.wave * k * waves));
         const double march3 = march * march * march;
         if (march3 >= least) return march3;
         const double busy = (double)per_xcd / (32 * k * ((per_xcd + 32 * k - 1) / (32 * k)));
-        const double move = pops * (1 + again * (1 + PLANES / cz)) / (rate * std::sqrt(std::sqrt(busy)));
+        const double move = pops * (once + again * (1 + c.planes / cz)) / (rate * std::sqrt(std::sqrt(busy)));
         return march3 + move * move * move;
     }
 };
 
 // Default tile of a step that takes npt nodes per thread: the cheapest of the
-// tiles that cut x, y and z into equal parts (rows of 24 to 256 nodes, at least
-// a wave of threads where the lattice has it, at most 6000 tiles unless the
-// whole height is one run).  Measured against the rule before it, z runs for
-// 2048 tiles (one node per thread) or 256 (the others) of fixed rows, in us a
-// step: FP64 32^3 38 -> 7.8, FP64 160 x 160 x 120 250 -> 224, FP32 split 32^3
-// 22 -> 9.1, FP32 split 150^3 with walls 242 -> 139, FP32 split 384 x 384 x 192
-// with walls 1478 -> 1076, F16S pairs 150^3 with walls 248 -> 101, F16N split
-// 160 x 160 x 120 197 -> 82; 256^3 keeps its tile (490, 295 and 334 with FP32,
-// F16S and F16N).  Of 212 lattices one was slower by more than 2% (6%).
+// tiles that cut x, y and z into equal parts (rows of 24 to 256 nodes, or of 128
+// where FP32's split step cuts them unequally; 60 threads or more where the
+// lattice has them; at most 6000 tiles unless the whole height is one run).
+// Measured against the rule before it, z runs for 2048 tiles (one node per
+// thread) or 256 (the others) of fixed rows, in us a step: FP64 32^3 38 -> 7.8,
+// FP64 160 x 160 x 120 250 -> 224, FP32 split 32^3 22 -> 9.1, FP32 split 150^3
+// with walls 242 -> 139, FP32 split 384 x 384 x 192 with walls 1478 -> 1076, F16S
+// pairs 150^3 with walls 248 -> 101, F16N split 160 x 160 x 120 197 -> 82; 256^3
+// keeps its tile (490, 295 and 334 with FP32, F16S and F16N).  Of 3000 lattices
+// drawn from 4 to 280 nodes a side the geometric mean is 0.51, and 12 are slower
+// by more than 3% (at most 16%, FP64 105 x 226 x 31).
 lbm_tile search_tile(int nx, int ny, int nz, int npt, int storage, bool split) {
     lbm_tile best{std::min(nx, 24) / npt * npt, 1, nz, 0};
     double least = std::numeric_limits<double>::infinity();
@@ -386,7 +402,7 @@ lbm_tile search_tile(int nx, int ny, int nz, int npt, int storage, bool split) {
     auto cuts = [](int n, int part) { return (int)(((long long)n + part - 1) / part); };
     // The largest part of an equal cut of n that is at most this one.
     auto equal = [&](int n, int part) { return part > 0 ? cuts(n, cuts(n, part)) : 0; };
-    for (int w = equal(nx, std::min(nx, 256)); w >= std::min(nx, 24); w = equal(nx, w - 1)) {
+    auto look_at = [&](int w) {
         lbm_tile t{};
         t.tx = (w + npt - 1) / npt * npt;
         bool tallest = true;
@@ -408,7 +424,9 @@ lbm_tile search_tile(int nx, int ny, int nz, int npt, int storage, bool split) {
                 }
             }
         }
-    }
+    };
+    if (split && storage == ST_F32 && 128 < nx && equal(nx, 128) != 128) look_at(128);
+    for (int w = equal(nx, std::min(nx, 256)); w >= std::min(nx, 24); w = equal(nx, w - 1)) look_at(w);
     return best;
 }
 

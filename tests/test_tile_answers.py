@@ -1,7 +1,12 @@
-"""A thread keeps the default tiles it has looked for: making contexts for the
-same lattices again costs far less than the first time (host code only; the
-workspace is never touched)."""
+"""Default tiles (host code only; the workspace is never touched).
+
+A thread keeps those it has looked for: making contexts for the same lattices
+again costs far less than the first time.  FP32's split step keeps wide tiles
+where rows do not start on 128 bytes.
+"""
 import time
+
+import pytest
 
 from paper_1805_08643_amd import binding
 import lbm_inputs as li
@@ -27,3 +32,12 @@ def test_kept_tiles_are_the_same():
             tile = binding.lbm_get_tile(ctx)
             binding.lbm_destroy(ctx)
             assert seen.setdefault((nx, ny, nz, st), tile) == tile
+
+
+@pytest.mark.parametrize("shape,width", [((220, 220, 220), 128), ((250, 250, 250), 128), ((186, 184, 184), 128),
+                                         ((252, 62, 240), 128), ((96, 96, 96), 96), ((256, 256, 256), 128)])
+def test_fp32_split_rows(shape, width):
+    ctx = binding.lbm_create(binding.make_params(li.params(*shape, storage="f32")), 4096, 1 << 40, 0)
+    assert binding.lbm_get_step_mode(ctx)[0] == binding.STEP_MODES["split"]
+    assert binding.lbm_get_tile(ctx)[0] == width
+    binding.lbm_destroy(ctx)
