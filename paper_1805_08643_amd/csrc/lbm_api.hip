@@ -510,6 +510,12 @@ unsigned grid1d(long long n, int threads, long long cap = 65536) {
     return (unsigned)std::max(1LL, std::min(b, cap));
 }
 
+// Blocks of the readback kernels that take their chunks in groups of eight
+// (k_psi_full's comment): a whole number of groups, so that none of the last
+// group's chunks is left for a second turn of the first blocks (FP32 fields of 48 x
+// 40 x 36, 270 chunks: 10.4 us with 270 blocks, 8.7 with 272).
+unsigned eights(unsigned blocks) { return (blocks + 7) / 8 * 8; }
+
 // Template dispatch over storage, operator and wall mode.
 template <class F> lbm_status dispatch(const lbm_ctx *c, F &&fn) {
     const int S = c->p.storage, O = c->p.op;
@@ -1048,7 +1054,7 @@ lbm_status lbm_read_fields(lbm_ctx *c, double *rho, double *u, double *p) {
     return dispatch(c, [&](auto S, auto, auto W) -> lbm_status {
         using T = typename Storage<S.value>::T;
         using R = typename Storage<S.value>::R;
-        hipLaunchKernelGGL((k_fields<S.value, W.value>), dim3(grid1d(c->g.N, 256)), dim3(256), 0, c->stream,
+        hipLaunchKernelGGL((k_fields<S.value, W.value>), dim3(eights(grid1d(c->g.N, 256))), dim3(256), 0, c->stream,
                            (const T *)c->state(), (const R *)c->psi(), (const R *)c->gpsi(), rho, u, p, c->g, c->pd);
         HIP_TRY(hipGetLastError());
         return LBM_OK;
@@ -1089,7 +1095,7 @@ lbm_status lbm_diagnostics(lbm_ctx *c, const lbm_diag_request *req, lbm_diag *ou
     }
     lbm_status s = compute_psi_full(c);
     if (s) return s;
-    const int nblk = (int)std::min<long long>(DIAG_BLOCKS, (c->g.N + DIAG_THREADS - 1) / DIAG_THREADS);
+    const int nblk = (int)eights(grid1d(c->g.N, DIAG_THREADS, DIAG_BLOCKS));
     s = dispatch(c, [&](auto S, auto, auto W) -> lbm_status {
         using T = typename Storage<S.value>::T;
         using R = typename Storage<S.value>::R;
