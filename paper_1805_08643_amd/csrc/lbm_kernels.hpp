@@ -1327,19 +1327,14 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
     constexpr bool NREF = S == ST_F16N;
     // F16N: whether the colliders leave a plane's stores in flight (see their
     // loop).  The walled and orthogonal kernels gain 5-31%; the periodic
-    // non-orthogonal one loses (406 against 341 us at 256^3), and so it does
-    // with the wrap of wrapi, which lets its pullers issue their loads sooner:
-    // waiting for the stores first is what it does best with, measured and not
-    // explained.
+    // non-orthogonal one loses (410 against 335 us at 256^3).
     constexpr bool AFLOAT = NREF && (WALL || OP == OP_ORTH);
-    auto wrap = [](int v, int n) {
-        if constexpr (NREF && !AFLOAT) {
-            const int r = v % n;
-            return r < 0 ? r + n : r;
-        } else {
-            return wrapi(v, n);
-        }
-    };
+    // That kernel is bound by its colliders' instructions, and its pullers hold
+    // back for some 200 cycles after each barrier while these start on their
+    // plane: 335 against 393 us at 256^3, 152 against 181 at 192^3, 50 against 54
+    // at 128^3, the same at 64^3.  A higher wave priority for the colliders
+    // instead gave 388, 157 and 52.
+    constexpr bool HOLD = NREF && !AFLOAT;
     auto &qbuf = L.qbuf;
     auto &ring = L.ring;
     const int TX = g.tx, TY = g.ty, TXG = g.tx / NPT;
@@ -1380,7 +1375,7 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
     const bool need_in = inner && xa <= nx && ly <= ny - y0;
     const bool active = inner && xa < nx && y0 + ly < ny;
     const int slot_q = AFLOAT && !puller ? ly * TXG + lx : rid;  // the group's slot in qbuf
-    const int gx = xa >= nx ? xa - nx : xa, gy = wrap(y0 + (inner ? ly : 0), ny);
+    const int gx = xa >= nx ? xa - nx : xa, gy = wrapi(y0 + (inner ? ly : 0), ny);
     const bool wl = gx == 0, wr = gx + NPT - 1 == nx - 1;
     const int cin = (ly + 1) * SX + NPT * lx + 1;
     const int nb = ly * TX + NPT * lx;  // first node slot in rbuf
@@ -1409,7 +1404,7 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
     bool halo[2];
     NbOff oh[2];
     auto setup = [&](const bool pull_role) {
-    oin.set(gx, wl, wr, gy, wrap(gy - 1, ny), wrap(gy + 1, ny), nx);
+    oin.set(gx, wl, wr, gy, wrapi(gy - 1, ny), wrapi(gy + 1, ny), nx);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const int h = pull_role ? rid + r * SPLIT_ROLE : rid + (r + 1) * SPLIT_ROLE;
@@ -1431,17 +1426,17 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
             }
             halo[r] = hlx <= nx - x0 && hly <= ny - y0;
         }
-        hxs[r] = wrap(x0 + hlx, nx);
-        hys[r] = wrap(y0 + hly, ny);
+        hxs[r] = wrapi(x0 + hlx, nx);
+        hys[r] = wrapi(y0 + hly, ny);
         chl[r] = (hly + 1) * SX + hlx + 1;
-        oh[r].set(hxs[r], wrap(hxs[r] - 1, nx), wrap(hxs[r] + 1, nx), hys[r], wrap(hys[r] - 1, ny),
-                  wrap(hys[r] + 1, ny), nx, E);
+        oh[r].set(hxs[r], wrapi(hxs[r] - 1, nx), wrapi(hxs[r] + 1, nx), hys[r], wrapi(hys[r] - 1, ny),
+                  wrapi(hys[r] + 1, ny), nx, E);
     }
     };
     // Colliding waves with a halo node in the first / second round (wave-uniform).
     const bool chw = RING2 && !puller && (int)__builtin_amdgcn_readfirstlane(rid) + SPLIT_ROLE < nh;
     const bool chw2 = RING2 && CR > 1 && !puller && (int)__builtin_amdgcn_readfirstlane(rid) + 2 * SPLIT_ROLE < nh;
-    auto zwrap = [&](int zp) { return WALL ? zp : wrap(zp, nz); };
+    auto zwrap = [&](int zp) { return WALL ? zp : wrap_plane(zp, nz); };
     auto rslot = [&](int z) { return ring[(z - zb + 1) & 3]; };
     auto nslot = [&](int z) -> uint16_t * {
         if constexpr (NREF) return L.nring[(z - zb + 1) & 3];
@@ -1640,6 +1635,7 @@ __device__ inline void tile_split(const typename Storage<S>::T *__restrict__ A, 
         setup(true);
         for (int i = 0; i < iters; ++i) {
             const int p = zb - 1 + i;
+            if constexpr (HOLD) __builtin_amdgcn_s_sleep(3);  // 3 x 64 cycles
             if (p <= ze) pull_plane(p);
             lds_barrier();
         }
