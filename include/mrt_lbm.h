@@ -262,11 +262,11 @@ lbm_status lbm_set_graph_steps(lbm_ctx *ctx, int32_t k);
  *   hip_stream: hipStream_t (NULL = default stream), borrowed; asynchronous.
  * It runs the step kernel and launch shape that a new context with these
  * parameters uses, so its result is bit for bit that of lbm_step.  Scratch
- * (the wall-plane densities and the Eq. (57) ghost psi planes, walls only)
- * lives in a device array inside the library, LBM_NOALLOC_SCRATCH_BYTES on
- * every GPU the library runs on, held until the process ends.  A walled
- * lattice whose planes need more (6 nx ny values, each plane set 256-byte
- * aligned) returns LBM_ERR_UNSUPPORTED before any HIP call.  The first call
+ * (the two Eq. (57) ghost psi planes and four planes that are reserved, walls
+ * on z only) lives in a device array inside the library,
+ * LBM_NOALLOC_SCRATCH_BYTES on every GPU the library runs on, held until the
+ * process ends.  A walled lattice whose planes need more (6 nx ny values, each
+ * plane set 256-byte aligned) returns LBM_ERR_UNSUPPORTED before any HIP call.  The first call
  * on a device looks up that device's array address (no allocation).  Calls
  * that overlap on one GPU share its scratch and race: serialise them (one
  * stream, or events). */
@@ -327,7 +327,7 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t trials, lbm_tile *best);
  * returns LBM_ERR_UNSUPPORTED.  With 2 or 4 nodes per thread the tile width
  * must be a multiple of that count (lbm_set_tile returns LBM_ERR_INVALID_ARG
  * otherwise); switching to a mode whose kernel cannot run the current tile
- * replaces the tile by the mode's default (rows of up to 128 nodes).
+ * replaces the tile by the mode's default (rows of up to 256 nodes).
  * slab_planes is used by LBM_STEP_SLABS only but must be >= 1.
  * All modes give the same populations bit for bit.  A new context uses
  * LBM_STEP_SPLIT where it applies, else LBM_STEP_PAIRS where that applies,
@@ -357,9 +357,9 @@ lbm_status lbm_set_write_check(lbm_ctx *ctx, int32_t enable);
  * cached).  LBM_STORE_AUTO (the default) stores non-temporally when the two
  * population arrays together exceed the GPU's 256 MiB last-level cache, where
  * cached stores would evict the lines the next plane's reads need (with walls
- * on x or y only if the direction planes start on 64 bytes); LBM_STORE_CACHED and LBM_STORE_STREAM force either
- * policy.  Results are bit for bit the same under every policy; only the
- * speed differs.  An unknown policy returns LBM_ERR_INVALID_ARG. */
+ * on x or y only if the direction planes start on 64 bytes); LBM_STORE_CACHED
+ * and LBM_STORE_STREAM force either policy.  Results are bit for bit the same
+ * under every policy; only the speed differs.  An unknown policy returns LBM_ERR_INVALID_ARG. */
 enum { LBM_STORE_AUTO = 0, LBM_STORE_CACHED = 1, LBM_STORE_STREAM = 2 };
 lbm_status lbm_set_store_policy(lbm_ctx *ctx, int32_t policy);
 lbm_status lbm_kernel_time(lbm_ctx *ctx, double *avg_ms, int64_t *launches);
@@ -407,7 +407,10 @@ lbm_status lbm_batch_set_blocks(lbm_batch *b, int32_t blocks);
  * the work list and drops captured graphs, and caps the grid at the new tile
  * count.  With lbm_batch_set_step_mode and lbm_batch_set_blocks it restores a
  * shape that lbm_batch_autotune chose (the tuning cache of the Python
- * binding does).  Results are bit for bit the same for every value. */
+ * binding does).  A batch whose items neither this nor lbm_batch_autotune has
+ * set chooses them itself, anew with every step mode: 8192 nodes, or with the
+ * split step one of 4096 to 32768 by the load of its blocks.  Results are bit
+ * for bit the same for every value. */
 lbm_status lbm_batch_set_item_nodes(lbm_batch *b, int32_t item_nodes);
 /* Current step mode, nodes per work item and grid size; any pointer may be NULL. */
 lbm_status lbm_batch_get_tuning(const lbm_batch *b, int32_t *mode, int32_t *item_nodes, int32_t *blocks);

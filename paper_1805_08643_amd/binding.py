@@ -461,7 +461,7 @@ class Lattice:
         return self
 
     def set_store_policy(self, policy):
-        """Split step's population stores: "auto", "cached" or "stream"."""
+        """Population stores of the split step and of runs with walls on x or y: "auto", "cached" or "stream"."""
         _call("lbm_set_store_policy", _vp(self.ctx), STORE_POLICIES[policy])
         return self
 
@@ -600,7 +600,7 @@ class Batch:
         return self
 
     def set_store_policy(self, policy):
-        """Split step's population stores: "auto", "cached" or "stream"."""
+        """Population stores of the split step and of runs with walls on x or y: "auto", "cached" or "stream"."""
         _call("lbm_batch_set_store_policy", _vp(self.h), STORE_POLICIES[policy])
         return self
 

@@ -190,7 +190,7 @@ Layout layout_of(const lbm_params &p) {
     off += pops;
     L.psi = off;
     off += align_up(N * real_bytes(p.storage));
-    L.rho_w = off;  // four planes that nothing uses now: part of the documented workspace and scratch sizes
+    L.rho_w = off;  // four reserved planes: part of the documented workspace and scratch sizes
     off += align_up(4 * plane * real_bytes(p.storage));
     L.gpsi = off;
     off += align_up(2 * plane * real_bytes(p.storage));
@@ -1027,7 +1027,7 @@ lbm_status lbm_step_noalloc(const lbm_params *p, const void *dev_src, void *dev_
     if (dev_src == dev_dst) return fail(LBM_ERR_INVALID_ARG, "source and destination must differ");
     if (reinterpret_cast<uintptr_t>(dev_src) % kAlign || reinterpret_cast<uintptr_t>(dev_dst) % kAlign)
         return fail(LBM_ERR_INVALID_ARG, "population buffers must be %zu-byte aligned", kAlign);
-    // Scratch: the wall-plane densities and the ghost psi planes (walls only).
+    // Scratch: the reserved and the ghost psi planes (walls only).
     const Layout L = layout_of(*p);
     const size_t need = p->wall_z ? L.partial - L.rho_w : 0;
     if (need > (size_t)LBM_NOALLOC_SCRATCH_BYTES)
