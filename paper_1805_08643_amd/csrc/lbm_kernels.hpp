@@ -318,11 +318,12 @@ __device__ inline void lds_barrier() {
 // have been taken.  For blocks of few waves of which a CU holds several; the
 // rule and what it measured are with the launch (paced_march).
 //
-// Bound by the address unit at about 70% of the time the compute units are
-// busy (8.4 cycles per wave access: rows that do not start on 64 bytes take
-// every access in two halves), the rest being the march's latency.  Against
-// divergent branches, wrapping divisions and a register copy per plane it
-// measured (best tile of a sweep each) 5.8 against 6.4 us at 32^3 and 132
+// Bound by the address unit at 78% of the time the compute units are busy (FP32
+// 100^3, 100 x 2 x 4 tiles, 35.7 us: 9.3 cycles per wave access, since rows that
+// do not start on 64 bytes take every access in two halves), the rest being the
+// march's latency; beyond the last-level cache by memory (150^3: 20 cycles).
+// Against divergent branches, wrapping divisions and a register copy per plane
+// it measured (best tile of a sweep each) 5.8 against 6.4 us at 32^3 and 132
 // against 146 at 150^3 in FP32, 7.8 against 8.5 at 32^3 and 1118 against 1154 at
 // 256^3 in FP64.
 template <int S, int OP, bool WALL, bool PACE = false>
@@ -2020,7 +2021,7 @@ __global__ void __launch_bounds__(WALL_THREADS)
 // Whole-lattice psi (for readback and diagnostics; not on the step path).
 // ---------------------------------------------------------------------------
 // psi of every node, for k_fields and k_diag, which read the same populations
-// again.  Bound by memory (84 us at FP64 128^3: 3.8 TB/s).  The two take their
+// again.  Bound by memory (74 us at FP64 128^3: 4.5 TB/s).  The two take their
 // chunks of nodes from the end, so that they begin with what this pass left in
 // the last-level cache, in groups of eight, so that a chunk stays on its XCD:
 // FP64 128^3 diagnostics and fields 370 -> 358 us.  In plain descending order
